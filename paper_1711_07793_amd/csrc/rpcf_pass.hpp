@@ -4,59 +4,40 @@
 // rbsm.hip.
 //
 // Every term of one fragment tests texels against the same depth, so the pass
-// first turns the fragment's (2r+3)^2 neighbourhood into shadow-test bits, one
-// 64-bit word per column (bit q <-> row j0-r-1+q).  A term's discontinuity
+// first turns the fragment's (2r+3)^2 neighbourhood into shadow-test bits: a
+// word per row and, transposed, a word per column.  A term's discontinuity
 // mask (Eq. 2-3) is then a few shifts and XORs, and the terms without a
-// discontinuity contribute their test result, so a column's worth of them is
-// one popcount.  Only the terms with a discontinuity need traversals
-// (Listing 3), normalization (Eq. 5) and Listing 5; their number varies
-// wildly between fragments, so such terms of each pair of columns are compacted
-// over the workgroup into an LDS list and evaluated one lane per term, keeping
-// every lane busy instead of holding a wave for its busiest fragment.  A
-// vertical traversal is first resolved on the fragment's column words, which
-// hold the shadow-test bits of every row it can reach inside the kernel's
-// window; horizontal ones take their first step from the neighbouring column's
-// word and their second from a staged band.  The
-// bands reach only a few steps past the window, which keeps the workgroup's
-// LDS small enough for more of them per CU; the few longer traversals go on
-// in global memory.
+// discontinuity contribute their test result, so a row's worth of them is one
+// popcount.  Only the terms with a discontinuity need traversals (Listing 3),
+// normalization (Eq. 5) and Listing 5; their number varies wildly between
+// fragments, so they are listed over a wave's 64 fragments and evaluated one
+// lane per term.  On the words a traversal is a shift and a count of ones.
+// The few that run out of the words before they stop are listed again and go
+// on in global memory.  A box too large for 32-bit words (r > 14) is done in
+// parts, one after the other.
 //
 // The average is the exact mean of the (2r+1)^2 binary32 terms, rounded to
-// binary32.  The terms are summed in binary64 (bit-word counts first, then the
-// listed terms in list order) and divided by (2r+1)^2 once: for at most 4225
-// terms in [0, 1] any binary64 summation order stays within 5e-13 of the exact
+// binary32.  Terms are summed as integers (multiples of 2^-52) and the sum is
+// divided by (2r+1)^2 once, in binary64: it stays within 5e-13 of the exact
 // mean, so the result is that mean rounded, up to one binary32 step at a
-// near-tie.
+// near-tie, and does not depend on the order of the terms.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "rbsm_device.hpp"
 #include "tile_pass.hpp"
 
 namespace rbsm {
 
-constexpr int kRpcfT = 128;    // threads per workgroup, one fragment each
-constexpr int kRpcfLaneBits = kRpcfT > 128 ? 8 : 7;  // lane field of a listed term
-constexpr int kRpcfMaxR = 30;  // largest r whose 2r+3 rows fit one 64-bit column word
-constexpr int kRpcfEnt = 512;  // terms with a discontinuity evaluated per round
-constexpr int kRpcfReach = 3;  // traversal steps staged beyond the kernel radius
-
-// Any radius: one lane per fragment, every term evaluated from global memory
-// in the same a-major order, binary64 sum.
-__global__ __launch_bounds__(256) void rpcf_naive_kernel(MapView m, const float *__restrict__ frags, int64_t n,
-                                                         float bias, int maxd, int r, float *__restrict__ out) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= n) return;
-    const float u = frags[3 * k + 0], v = frags[3 * k + 1], z = frags[3 * k + 2];
-    const Addr a = address(u, v, z, m.W, m.H, bias);
-    double sum = 0.0;
-    for (int da = -r; da <= r; ++da)
-        for (int db = -r; db <= r; ++db)
-            sum += (double)eval_texel<false>(m, a.i0 + da, a.j0 + db, a.fx, a.fy, a.zb, maxd);
-    out[k] = (float)(sum / (double)((2 * r + 1) * (2 * r + 1)));
-}
+constexpr int kRpcfT = 128;      // threads per workgroup, one fragment each
+constexpr int kWinMaxR = 14;     // largest r whose 2r+3 rows and columns fit 32-bit words
+constexpr int kWinPart = 22;     // beyond it: terms per side of a part, at most
+constexpr int kWinLate = 128;    // terms per wave with a traversal that leaves the window
 
 // Shadow-test bit of texel depth t for depth zb (Eq. 1): the sign bit of
 // t - zb.  The difference is negative exactly when zb > t, except for
@@ -66,48 +47,7 @@ __device__ __forceinline__ uint32_t push_bit(uint32_t w, float t, float zb) {
     return __builtin_amdgcn_alignbit(w, __float_as_uint(t - zb), 31);  // (w << 1) | sign
 }
 
-// Shadow-test bits of nb <= 64 texels: bit p is 1 when texel p, read by
-// rd(p), is in shadow for depth zb.  Reads run in chunks of 8 up to the next
-// multiple of 8, so rd must accept p that far; the bits at and above nb are
-// cleared.
-template <class Rd>
-__device__ __forceinline__ uint64_t shadow_bits(Rd rd, int nb, float zb) {
-    const int nb8 = (nb + 7) & ~7;
-    uint32_t hi = 0, lo = 0;
-    for (int c = nb8 - 8; c >= 32; c -= 8) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = rd(c + e);
-#pragma unroll
-        for (int e = 7; e >= 0; --e) hi = push_bit(hi, v[e], zb);
-    }
-    for (int c = min(nb8, 32) - 8; c >= 0; c -= 8) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = rd(c + e);
-#pragma unroll
-        for (int e = 7; e >= 0; --e) lo = push_bit(lo, v[e], zb);
-    }
-    const uint64_t all = ((uint64_t)hi << 32) | lo;
-    return nb >= 64 ? all : all & ((1ull << nb) - 1ull);
-}
-
 __device__ __forceinline__ float canon(float t) { return t != t ? __builtin_inff() : t + 0.0f; }
-
-typedef __attribute__((address_space(3))) const char lds_byte;
-
-// Three texel lines of a staged band, read at one offset: the line a
-// traversal moves along and its two side lines.
-struct BandWalkReader {
-    lds_byte *c, *a, *b;
-    unsigned step;  // bytes per unit of p
-    __device__ __forceinline__ void operator()(int p, float &tc, float &ta, float &tb) const {
-        const unsigned x = step * (unsigned)p;
-        tc = *(const lds_float *)(c + x);
-        ta = *(const lds_float *)(a + x);
-        tb = *(const lds_float *)(b + x);
-    }
-};
 
 // A map line and its two side lines (rows c, a, b when horizontal, columns
 // when not), read from global memory with clamp-to-edge.
@@ -122,387 +62,486 @@ struct MapLineReader {
     }
 };
 
-// The first two steps of a horizontal traversal (Listing 3), with no branches
-// so that the reads of all four traversals of a term can be in flight
-// together: step 1 from w1, the shadow-test word of the neighbouring column in
-// the walk's direction (bit q the term's row, q + 1 and q - 1 its side rows,
-// bit 1 = in shadow), step 2 from the staged band.  +k / -k for the first
-// stopping step, 0 if neither stops.
-__device__ __forceinline__ int first_steps(const BandWalkReader &br, uint64_t w1, int q, int p0, int d, int maxd,
-                                           float zb, bool s, bool chk_a, bool chk_b) {
-    float c2, a2, b2;
-    br(p0 + (maxd >= 2 ? 2 * d : d), c2, a2, b2);
-    const uint64_t v = s ? w1 : ~w1;  // bit set: that texel's test differs from the term's
-    const bool end1 = (v >> q) & 1ull, end2 = (zb > c2) == s;
-    const bool share1 = (chk_a & (bool)((v >> (q + 1)) & 1ull)) | (chk_b & (bool)((v >> (q - 1)) & 1ull));
-    const bool share2 = (chk_a & ((zb > a2) == s)) | (chk_b & ((zb > b2) == s));
-    const int at2 = maxd >= 2 ? (end2 ? 2 : (share2 ? 0 : -2)) : 0;
-    return end1 ? 1 : (share1 ? at2 : -1);
-}
+// A word of NR bits.
+template <int NR>
+struct WinWord {
+    using T = typename std::conditional<(NR <= 16), uint16_t, uint32_t>::type;
+};
 
-// Stop rows of a vertical traversal over the column words w (the term's
-// column) and wl, wr (its left and right neighbours), bit 1 = in shadow: bit
-// p of `end` is set where the texel of row p has a test that differs from the
-// term's s (its bit equals s), and bit p of the result where the walk stops
-// there: it ends, or no checked neighbour's texel differs from s.
-__device__ __forceinline__ uint64_t stop_bits(uint64_t wl, uint64_t w, uint64_t wr, bool s, bool chk_l, bool chk_r,
-                                              uint64_t &end) {
-    const uint64_t flip = s ? 0ull : ~0ull;
-    end = w ^ flip;
-    const uint64_t share = (chk_l ? wl ^ flip : 0ull) | (chk_r ? wr ^ flip : 0ull);
-    return end | ~share;
-}
-
-// A vertical traversal (Listing 3) of the term in row q of column word w, as
-// far as the word reaches, up (rows q+1, ...) or down (rows q-1, ...): +k / -k
-// for the first stopping step, -(maxd+1) when the walk runs out of steps
-// inside the word, or 0 with `next` set to the first step past the word.
-__device__ __forceinline__ int column_walk_up(uint64_t wl, uint64_t w, uint64_t wr, int q, int nbc, int maxd, bool s,
-                                              bool chk_l, bool chk_r, int &next) {
-    uint64_t end;
-    const uint64_t stop = stop_bits(wl, w, wr, s, chk_l, chk_r, end);
-    const int kn = min(nbc - 1 - q, maxd);  // steps inside the word, >= 1
-    const uint64_t b = (stop >> (q + 1)) & ((1ull << kn) - 1ull);
-    next = kn + 1;
-    if (b != 0ull) {
-        const int k = __builtin_ctzll(b) + 1;
-        return (end >> (q + k)) & 1ull ? k : -k;
+// Transposes the S x S bit matrix a (bit x of a[y] becomes bit y of a[x]),
+// S = 16 or 32, swapping blocks of J bits, then of J / 2, ...; words of a
+// known to be zero fold away.
+template <int S, int J = S / 2>
+__device__ __forceinline__ void transpose_bits(uint32_t (&a)[S]) {
+    // the bits whose position has bit J clear
+    constexpr uint32_t m = J == 16  ? 0x0000ffffu
+                           : J == 8 ? 0x00ff00ffu
+                           : J == 4 ? 0x0f0f0f0fu
+                           : J == 2 ? 0x33333333u
+                                    : 0x55555555u;
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        if (k & J) continue;
+        const uint32_t p = a[k], q = a[k + J];
+        a[k] = (p & m) | ((q << J) & ~m);
+        a[k + J] = ((p >> J) & m) | (q & ~m);
     }
-    return kn == maxd ? -(maxd + 1) : 0;
+    if constexpr (J > 1) transpose_bits<S, J / 2>(a);
 }
 
-__device__ __forceinline__ int column_walk_down(uint64_t wl, uint64_t w, uint64_t wr, int q, int maxd, bool s,
-                                                bool chk_l, bool chk_r, int &next) {
-    uint64_t end;
-    const uint64_t stop = stop_bits(wl, w, wr, s, chk_l, chk_r, end);
-    const int kn = min(q, maxd);  // steps inside the word (rows q-1 .. q-kn), >= 1
-    const uint64_t b = stop & (((1ull << kn) - 1ull) << (q - kn));
-    next = kn + 1;
-    if (b != 0ull) {
-        const int p = 63 - __builtin_clzll(b);  // nearest stopping row below q
-        const int k = q - p;
-        return (end >> p) & 1ull ? k : -k;
-    }
-    return kn == maxd ? -(maxd + 1) : 0;
+// Steps and outcome of one traversal: it goes on for `go` steps and stops at
+// the next, ending the edge there or not (after maxd steps: not).
+struct WalkEnd {
+    int go;
+    uint32_t end;  // 1: step go + 1 ends the edge
+};
+
+// The coordinate of Eq. 5 on one axis from its two traversals (n towards
+// smaller, p towards larger coordinates), as normalize_axis and the code-1
+// rule of vis_rsmss: with exactly one end the distance over the length, 1 with
+// none, 0 with two.  The quotient comes from the correctly rounded reciprocal
+// of the length and one residual step, which gives the correctly rounded
+// quotient (checked for every significand over every length up to 129; a
+// position below 2^-100 may lose denormal bits).
+__device__ __forceinline__ float win_axis(WalkEnd n, WalkEnd p, float f, const lds_float *rcp) {
+    const int len = n.go + p.go + 1;
+    const float a = (float)(p.end ? p.go + 1 : n.go) + (p.end ? -f : f);
+    const float y = rcp[len];
+    const float q0 = a * y;
+    const float q = __builtin_fmaf(__builtin_fmaf(-q0, (float)len, a), y, q0);
+    // selected with masks, not a select: no branch splits the reads above
+    const uint32_t one = 0u - (n.end ^ p.end), none = (n.end | p.end) - 1u;
+    return __uint_as_float((__float_as_uint(q) & one) | (0x3f800000u & none));
 }
 
-// One workgroup per TW x (kRpcfT / TW) pixel tile of a row-major image of
-// width vw (flat: vw = n, TW = kRpcfT).  With R = r + min(maxd, kRpcfReach),
-// the texels every word and the first R - r steps of every traversal read lie
-// in bands staged in LDS (with canon() applied) when they fit in `cap`
-// texels; longer traversals go on in global memory:
-//   H: rows of the fragments' texel box grown by r+1, columns grown by R
-//      (row-major; horizontal traversals);
-//   V (VB): columns grown by r+1, rows grown by R, stored transposed, each
-//      column contiguous (column words and vertical traversals).
-// Without V, column words read H down its columns (7 more rows staged for the
-// chunked reads) and vertical traversals use H's rows: half the LDS, so more
-// workgroups per CU, for slower column reads and a shorter vertical reach.
-// Band coordinates are unclamped positions holding clamped texels, so no read
-// clamps.  Otherwise everything reads global memory.  Requires 1 <= r <=
-// kRpcfMaxR.  At most 128 VGPRs (4 waves per SIMD): the H-only form would
-// take 154 (3 waves) and runs 5-12% faster held to 128, a few values spilled.
-template <int TW, bool VB>
-__global__ __launch_bounds__(kRpcfT) __attribute__((amdgpu_waves_per_eu(4))) void rpcf_kernel(MapView m, const float *__restrict__ frags, int64_t n,
-                                                      int64_t vw, int64_t tiles_x, float bias, int maxd, int r,
-                                                      int cap, float *__restrict__ out) {
-    extern __shared__ float s_band[];
-    __shared__ int s_red[kRpcfT / 64][4];
-    __shared__ int s_wtot[2][kRpcfT / 64];
-    __shared__ int s_fi[kRpcfT], s_fj[kRpcfT];
-    __shared__ float s_ffx[kRpcfT], s_ffy[kRpcfT], s_fzb[kRpcfT];
-    __shared__ uint32_t s_ent[kRpcfEnt];  // lane | q << LB | lit << (LB+6) | mask << (LB+7) | column << (LB+11)
-    __shared__ float s_val[kRpcfEnt];
-    __shared__ uint64_t s_cw[4][kRpcfT];  // this round's column words a-1 .. a+2 of each fragment
-    constexpr int TH = kRpcfT / TW, LB = kRpcfLaneBits;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
+// One wave per 64 fragments (two waves per workgroup share a staged band).
+//
+// Each lane tests its fragment's NR x NR window (NR >= 2r+3 texels square,
+// the (2r+3)^2 neighbourhood and up to a few texels more on each side) into
+// NR row words, transposed in registers into NR column words; both stay in
+// LDS, [word][lane].  With them every traversal of a term is a shift and a
+// count of ones: along its row word for the horizontal pair, along its column
+// word for the vertical pair.  The terms with a discontinuity of the wave's 64
+// fragments are listed in LDS lane by lane round-robin (row by row, a ballot
+// and a popcount per listed term of a lane, so no scan and no barrier), and
+// evaluated one lane per term in full waves.  Neighbouring list entries belong
+// to different fragments, so the words are read and the results added
+// without bank or address conflicts.  A term with a traversal that runs out
+// of the window before it stops goes to a second list and is finished from
+// global memory, again in full waves.
+//
+// Results are summed as integers: a term v in [0, 1] adds the bits of 1 + v
+// (binary64), a multiple of 2^-52, so the sum does not depend on the order of
+// the list, and each term is rounded by at most 2^-53.
+//
+// A wave whose fragments all pass, or all fail, every test of the band (the
+// band's depth range against theirs) is done at once: the mean is 1 or 0.
+//
+// MULTI: the (2r+1)^2 box in parts x parts parts of part_side terms a side
+// (the last ones fewer), each with its own window, summed one after the other.
+//
+// Bound by VALU issue (about 120 instructions a listed term, 2 a test) and,
+// where the words leave LDS for 8 to 10 waves per CU (r >= 11), by latency.
+// Against one lane per term with per-step walks on a staged band and 64-bit
+// column words (two scenes each): 4K fenced frame r = 5 0.87 / 1.71 ms ->
+// 0.46 / 0.63, 1080p r = 13 2.23 / 1.75 -> 1.09 / 0.99, 720p r = 15 2.11 / 3.31
+// -> 0.88 / 0.88, 640x360 r = 32 (one lane per fragment before) 26.5 -> 1.4.
+// Keeping both kinds of words at 16 bits up to NR = 16 gives 28 waves per CU.
+template <int NR, bool MULTI>
+__global__ __launch_bounds__(kRpcfT) __attribute__((amdgpu_waves_per_eu(NR <= 16 ? 7 : 4))) void
+rpcf_window_kernel(
+    MapView m, const float *__restrict__ frags, int64_t n, int64_t vw, int64_t tiles_x, int tw_log2, float bias,
+    int maxd, int r, int parts, int part_side, int cap, int list_cap, int chunk_log2, float *__restrict__ out) {
+    using Word = typename WinWord<NR>::T;
+    constexpr int S = NR <= 16 ? 16 : 32;  // transposed size
+    constexpr uint32_t kAll = NR == 32 ? 0xffffffffu : (1u << (NR & 31)) - 1u;
+    // Dynamic LDS.  Of the NR rows and columns N = side + 2 stay (all NR in 16-bit
+    // words, which leave LDS enough):
+    //   row words [wave][N][lane], those of rows c0 - 1 .. c0 + side;
+    //   the other rows' words of wave 0, the band (cap texels), the other
+    //   rows' words of wave 1: all overwritten by column words [wave][N][lane]
+    //   (columns c0 - 1 .. c0 + side), each wave's own words by its own;
+    //   the reciprocals of the edge lengths 1 .. 2 maxd + 1;
+    //   the lists of terms [wave][list_cap]
+    extern __shared__ char s_dyn[];
+    __shared__ int s_red[2][6];
+    __shared__ unsigned long long s_sum[kRpcfT];
+    __shared__ uint16_t s_late[2][kWinLate];
+    const int side = MULTI ? part_side : 2 * r + 1;
+    const int N = NR <= 16 ? NR : side + 2, xwords = (NR - N) * 64;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int tw = 1 << tw_log2, th = kRpcfT >> tw_log2;
+    const int64_t tile = xcd_chunked(blockIdx.x, gridDim.x, chunk_log2);
     const int64_t tyi = tile / tiles_x, txi = tile - tyi * tiles_x;
-    const int64_t px = txi * TW + (t % TW), py = tyi * TH + (t / TW);
+    const int64_t px = (txi << tw_log2) + (t & (tw - 1)), py = tyi * th + (t >> tw_log2);
     const int64_t k = py * vw + px;
     const bool valid = px < vw && k < n;
     Addr A{};
-    if (valid) A = address(frags[3 * k + 0], frags[3 * k + 1], frags[3 * k + 2], m.W, m.H, bias);
-    const int R = r + min(maxd, kRpcfReach);
+    if (valid) A = address(gld(frags + 3 * k), gld(frags + 3 * k + 1), gld(frags + 3 * k + 2), m.W, m.H, bias);
+    Word *const words = reinterpret_cast<Word *>(s_dyn);  // wave 0's row words, wave 1's, wave 0's column words
+    float *const band = reinterpret_cast<float *>(words + 128 * N + xwords);
+    Word *const xrows = wave == 0 ? words + 128 * N : reinterpret_cast<Word *>(band + cap);
+    float *const s_rcp = reinterpret_cast<float *>(reinterpret_cast<Word *>(band + cap) + xwords);
+    for (int l = t + 1; l <= 2 * maxd + 1; l += kRpcfT) s_rcp[l] = 1.0f / (float)l;
 
     // texel box of the tile's fragments
-    int b0 = valid ? A.i0 : INT32_MAX, b1 = valid ? -A.i0 : INT32_MAX;
-    int b2 = valid ? A.j0 : INT32_MAX, b3 = valid ? -A.j0 : INT32_MAX;
-    for (int o = 32; o >= 1; o >>= 1) {
-        b0 = min(b0, __shfl_xor(b0, o));
-        b1 = min(b1, __shfl_xor(b1, o));
-        b2 = min(b2, __shfl_xor(b2, o));
-        b3 = min(b3, __shfl_xor(b3, o));
+    {
+        const int b0 = wave_min(valid ? A.i0 : INT32_MAX), b1 = wave_min(valid ? -A.i0 : INT32_MAX);
+        const int b2 = wave_min(valid ? A.j0 : INT32_MAX), b3 = wave_min(valid ? -A.j0 : INT32_MAX);
+        if (lane == 0) {
+            s_red[wave][0] = b0;
+            s_red[wave][1] = b1;
+            s_red[wave][2] = b2;
+            s_red[wave][3] = b3;
+        }
     }
-    if (lane == 0) {
-        s_red[wave][0] = b0;
-        s_red[wave][1] = b1;
-        s_red[wave][2] = b2;
-        s_red[wave][3] = b3;
-    }
-    s_fi[t] = A.i0;
-    s_fj[t] = A.j0;
-    s_ffx[t] = A.fx;
-    s_ffy[t] = A.fy;
-    s_fzb[t] = A.zb;
+    s_sum[t] = 0ull;
     __syncthreads();
-    for (int w = 0; w < kRpcfT / 64; ++w) {
-        b0 = min(b0, s_red[w][0]);
-        b1 = min(b1, s_red[w][1]);
-        b2 = min(b2, s_red[w][2]);
-        b3 = min(b3, s_red[w][3]);
-    }
+    const int b0 = __builtin_amdgcn_readfirstlane(min(s_red[0][0], s_red[1][0]));
+    const int b1 = __builtin_amdgcn_readfirstlane(min(s_red[0][1], s_red[1][1]));
+    const int b2 = __builtin_amdgcn_readfirstlane(min(s_red[0][2], s_red[1][2]));
+    const int b3 = __builtin_amdgcn_readfirstlane(min(s_red[0][3], s_red[1][3]));
     if (b0 == INT32_MAX) return;  // no fragment in this tile (uniform)
-    const int nbc = 2 * r + 3;    // bits of a column word
-    const int fw = (-b1) - b0, fh = (-b3) - b2;  // texel box extent - 1
-    const int hx = b0 - R, hy = b2 - r - 1;
-    const int hw = fw + 2 * R + 1, hh = fh + 2 * r + 3;
-    // column words read 8 texels at a time: up to 7 more rows; an odd column
-    // length keeps the transposing stores conflict-free
-    const int vx = b0 - r - 1, vy = b2 - R;
-    const int vwd = fw + 2 * r + 3, vh = (fh + 2 * R + 1 + 7) | 1;
-    const int hrows = VB ? hh : hh + 7;  // without V, column words read whole chunks of 8 rows of H
-    const bool staged = (int64_t)hw * hrows + (VB ? (int64_t)vwd * vh : 0) <= cap;
-    float *hb = s_band, *vb = s_band + (staged ? hw * hrows : 0);
-    if (staged) {
-        {
-            const int area = hw * hrows;
-            int y = t / hw, x = t % hw;
-            const int dy = kRpcfT / hw, dx = kRpcfT % hw;
-            for (int idx = t; idx < area; idx += kRpcfT) {
-                hb[idx] = canon(texel(m, hx + x, hy + y));
-                y += dy;
-                x += dx;
-                if (x >= hw) {
-                    x -= hw;
-                    ++y;
-                }
-            }
-        }
-        if (VB) {
-            // read row by row (coalesced), store transposed
-            const int area = vwd * vh;
-            int y = t / vwd, x = t % vwd;
-            const int dy = kRpcfT / vwd, dx = kRpcfT % vwd;
-            for (int idx = t; idx < area; idx += kRpcfT) {
-                vb[x * vh + y] = canon(texel(m, vx + x, vy + y));
-                y += dy;
-                x += dx;
-                if (x >= vwd) {
-                    x -= vwd;
-                    ++y;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const lds_float *hbl = (const lds_float *)hb, *vbl = (const lds_float *)vb;
 
-    // shadow-test bits of column i, rows j0-r-1 .. j0+r+1
-    auto colword = [&](int i) -> uint64_t {
-        if (!valid) return 0ull;
-        if (staged) {
-            if constexpr (VB) {
-                const lds_float *line = vbl + (i - vx) * vh + (A.j0 - r - 1 - vy);
-                return shadow_bits([&](int q) { return line[q]; }, nbc, A.zb);
-            } else {
-                const lds_float *col = hbl + (A.j0 - r - 1 - hy) * hw + (i - hx);
-                return shadow_bits([&](int q) { return col[q * hw]; }, nbc, A.zb);
-            }
-        }
-        const int j = A.j0 - r - 1;
-        return shadow_bits([&](int q) { return canon(texel(m, i, j + q)); }, nbc, A.zb);
+    // the window: its part of the kernel's box at positions c0, c0 + 1, ...
+    const int c0 = 1 + ((NR - (side + 2)) >> 1);
+    const int64_t hw64 = (int64_t)(-b1) - b0 + NR, hh64 = (int64_t)(-b3) - b2 + NR;
+    const bool staged = hw64 * hh64 <= cap;
+    const int hw = (int)hw64, hh = (int)hh64;
+    // this lane's words of row / column k0, k0 + 1, ...
+    const int k0 = NR <= 16 ? 0 : c0 - 1;
+    Word *const rw = words + wave * (64 * N) + lane, *const cw = rw + 128 * N;
+    // where the word of row y of the window is until the columns are made
+    auto row_at = [&](int y) -> Word * {
+        const int q = y - k0;
+        if (q >= 0 && q < N) return rw + q * 64;
+        return xrows + lane + (q < 0 ? y : y - N) * 64;  // rows 0 .. k0 - 1, then k0 + N .. NR - 1
     };
-
-    const uint64_t range = ((1ull << (2 * r + 1)) - 1ull) << 1;  // rows j0-r .. j0+r
-    double acc = 0.0;
-    // two columns per round, a and a + 1: words cm (a-1), c0 (a), c1 (a+1), c2 (a+2)
-    uint64_t cm = colword(A.i0 - r - 1), c0 = colword(A.i0 - r);
-    for (int a = -r; a <= r; a += 2) {
-        const bool two = a + 1 <= r;  // uniform
-        const uint64_t c1 = colword(A.i0 + a + 1);
-        const uint64_t c2 = two ? colword(A.i0 + a + 2) : 0ull;
-        // discontinuity masks of column x (words w_-, w, w_+): L, R, T, B
-        const uint64_t e0 = valid ? ((c0 ^ cm) | (c0 ^ c1) | (c0 ^ (c0 >> 1)) | (c0 ^ (c0 << 1))) & range : 0ull;
-        const uint64_t e1 =
-            valid && two ? ((c1 ^ c0) | (c1 ^ c2) | (c1 ^ (c1 >> 1)) | (c1 ^ (c1 << 1))) & range : 0ull;
-        // terms without a discontinuity: their own test (lit = 1)
-        acc += (double)__builtin_popcountll(~e0 & ~c0 & range);
-        if (two) acc += (double)__builtin_popcountll(~e1 & ~c1 & range);
-
-        // this round's terms with a discontinuity: offsets over the workgroup
-        const int n0 = __builtin_popcountll(e0), ne = n0 + __builtin_popcountll(e1);
-        int inc = ne;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(inc, o);
-            if (lane >= o) inc += y;
-        }
-        const int par = ((a + r) >> 1) & 1;  // double buffer: no barrier between rounds without such terms
-        if (lane == 63) s_wtot[par][wave] = inc;
-        // the previous round's readers of s_cw all passed its last barrier
-        s_cw[0][t] = cm;
-        s_cw[1][t] = c0;
-        s_cw[2][t] = c1;
-        s_cw[3][t] = c2;
-        __syncthreads();
-        int off = inc - ne, tot = 0;
-        for (int w = 0; w < kRpcfT / 64; ++w) {
-            const int x = s_wtot[par][w];
-            off += w < wave ? x : 0;
-            tot += x;
-        }
-        for (int w0 = 0; w0 < tot; w0 += kRpcfEnt) {  // uniform
-            const int cnt = min(kRpcfEnt, tot - w0);
-            // list this lane's terms that fall in [w0, w0 + cnt): column a, then a + 1
-            if (off < w0 + cnt && off + ne > w0) {
-                int e = off;
-                for (int x = 0; x < 2; ++x) {
-                    const uint64_t wl = x ? c0 : cm, w = x ? c1 : c0, wr = x ? c2 : c1;
-                    uint64_t bits = x ? e1 : e0;
-                    for (; bits; ++e) {
-                        const int q = __builtin_ctzll(bits);
-                        bits &= bits - 1ull;
-                        if (e < w0 || e >= w0 + cnt) continue;
-                        const uint32_t mk = (uint32_t)(((w ^ wl) >> q) & 1ull) * BIT_L |
-                                            (uint32_t)(((w ^ wr) >> q) & 1ull) * BIT_R |
-                                            (uint32_t)(((w ^ (w >> 1)) >> q) & 1ull) * BIT_T |
-                                            (uint32_t)(((w ^ (w << 1)) >> q) & 1ull) * BIT_B;
-                        const uint32_t lit_ = ((w >> q) & 1ull) == 0ull ? 1u : 0u;
-                        s_ent[e - w0] = (uint32_t)t | (uint32_t)q << LB | lit_ << (LB + 6) | mk << (LB + 7) |
-                                        (uint32_t)x << (LB + 11);
+    int lit_terms = 0, edge_terms = 0;  // of this lane
+    // One part of the box.  True where every lane's tests are all the same
+    // (plain_lit: lit), which its terms then are.
+    auto run_part = [&](int part, bool &plain_lit) -> bool {
+        const int px0 = MULTI ? (part % parts) * side : 0, py0 = MULTI ? (part / parts) * side : 0;
+        const int nx = MULTI ? min(side, 2 * r + 1 - px0) : side, ny = MULTI ? min(side, 2 * r + 1 - py0) : side;
+        const int ox = px0 - r - c0, oy = py0 - r - c0;  // the window's first texel, from the fragment's
+        const int hx = b0 + ox, hy = b2 + oy;
+        if (MULTI && part > 0) __syncthreads();  // the last part's column words are read: the band overwrites them
+        bool lit_all = false, dark_all = false;
+        if (staged) {
+            // one column per lane, rows alternating between the waves, 8 loads in flight
+            float lo_t = __builtin_inff(), hi_t = -__builtin_inff();
+            for (int xb = 0; xb < hw; xb += 64) {
+                const int x = min(xb + lane, hw - 1);
+                const int gx = clampi(hx + x, m.W);
+                for (int yb = wave; yb < hh; yb += 16) {
+                    float v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)  // rows past the band re-read its last one
+                        v[u] = gld(m.t + (int64_t)clampi(hy + min(yb + 2 * u, hh - 1), m.H) * m.pitch + gx);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const float c = canon(v[u]);
+                        lo_t = fminf(lo_t, c);
+                        hi_t = fmaxf(hi_t, c);
+                        if (yb + 2 * u < hh && xb + lane < hw) band[(yb + 2 * u) * hw + x] = c;
                     }
                 }
             }
+            // signed integers in the order of the depths
+            auto ord = [](float f) {
+                const int b = __float_as_int(f);
+                return b ^ ((b >> 31) & 0x7fffffff);
+            };
+            const int tmin = wave_min(ord(lo_t)), tmax = wave_min(-ord(hi_t));
+            const float z = A.zb + 0.0f;  // -0 as +0
+            const int zmax = -wave_min(valid ? -ord(z) : INT32_MAX), zmin = wave_min(valid ? ord(z) : INT32_MAX);
+            if (lane == 0) {
+                s_red[wave][4] = tmin;
+                s_red[wave][5] = tmax;
+            }
             __syncthreads();
-            // one lane per term: its four traversals, normalization (Eq. 5) and Listing 5
-            for (int e = t; e < cnt; e += kRpcfT) {
-                const uint32_t en = s_ent[e];
-                const int L = en & ((1u << LB) - 1u), q = (en >> LB) & 63;
-                const bool s = (en >> (LB + 6)) & 1u;
-                const unsigned mk = (en >> (LB + 7)) & 15u;
-                const int i = s_fi[L] + a + (int)((en >> (LB + 11)) & 1u), j = s_fj[L] - r - 1 + q;
-                const float zb = s_fzb[L];
-                int rd[4];  // left, right, top, bottom
+            lit_all = zmax <= min(s_red[0][4], s_red[1][4]);
+            dark_all = zmin > -min(s_red[0][5], s_red[1][5]);
+        } else {
+            __syncthreads();
+        }
+        // every window of the tile inside the map
+        const bool inside = hx >= 0 && hy >= 0 && hx + hw64 <= m.W && hy + hh64 <= m.H;
+        // row words (bit x: texel hx + x of the row is in shadow)
+        const bool done = (bool)__builtin_amdgcn_readfirstlane((int)(lit_all || dark_all));
+        uint32_t any = 0u, every = kAll;
+        if (!done) {
+            const lds_float *line = (const lds_float *)band + (valid ? (A.j0 - b2) * hw + (A.i0 - b0) : 0);
+            for (int y = 0; y < NR; ++y) {
+                uint32_t w = 0u;
+                float v[NR];
                 if (staged) {
-                    // H: rows j, j+1 (top), j-1 (bottom) along columns;
-                    // V: columns i, i-1 (left), i+1 (right) along rows
-                    // (without V: H down column i, the side columns at -+1)
-                    const lds_float *ph = hbl + (j - hy) * hw;
-                    const lds_float *pv = VB ? vbl + (i - vx) * vh : hbl + (i - hx);
-                    const int vside = VB ? vh : 1;
-                    BandWalkReader bh, bv;
-                    bh.c = (lds_byte *)ph;
-                    bh.a = (lds_byte *)(ph + hw);
-                    bh.b = (lds_byte *)(ph - hw);
-                    bh.step = 4u;
-                    bv.c = (lds_byte *)pv;
-                    bv.a = (lds_byte *)(pv - vside);
-                    bv.b = (lds_byte *)(pv + vside);
-                    bv.step = VB ? 4u : 4u * (unsigned)hw;
-                    const int ph0 = i - hx, pv0 = VB ? j - vy : j - hy;
-                    const int vlen = VB ? vh : hrows;  // band positions of a vertical traversal
-                    const bool ht = (mk & BIT_T) != 0, hbt = (mk & BIT_B) != 0;
-                    const bool vl = (mk & BIT_L) != 0, vr = (mk & BIT_R) != 0;
-                    // the fragment's column words of the term's column and its
-                    // neighbours (rows j0-r-1 .. j0+r+1): the horizontal
-                    // traversals' first steps, and the vertical ones as far
-                    // as the words reach
-                    const int x = (en >> (LB + 11)) & 1u;
-                    const uint64_t wl = s_cw[x][L], w = s_cw[x + 1][L], wr = s_cw[x + 2][L];
-                    rd[0] = first_steps(bh, wl, q, ph0, -1, maxd, zb, s, ht, hbt);
-                    rd[1] = first_steps(bh, wr, q, ph0, 1, maxd, zb, s, ht, hbt);
-                    int k0[4] = {3, 3, 0, 0};
-                    rd[2] = column_walk_up(wl, w, wr, q, nbc, maxd, s, vl, vr, k0[2]);
-                    rd[3] = column_walk_down(wl, w, wr, q, maxd, s, vl, vr, k0[3]);
-                    // the few that run on
-                    for (int dir = 0; dir < 4; ++dir) {
-                        if (rd[dir] != 0) continue;
-                        const bool horiz = dir < 2;
-                        const int d = dir == 0 || dir == 3 ? -1 : 1;
-                        const int p0 = horiz ? ph0 : pv0;
-                        const bool ca = horiz ? ht : vl, cb = horiz ? hbt : vr;
-                        // last step inside the band
-                        const int kl = min(maxd, d > 0 ? (horiz ? hw : vlen) - 1 - p0 : p0);
-                        int x = 0;
-                        if (k0[dir] <= kl)
-                            x = walk_range<4>(horiz ? bh : bv, k0[dir], kl, p0, d, INT32_MAX / 4, zb, s, ca, cb);
-                        if (x == 0 && kl < maxd) {
-                            const MapLineReader g{m, horiz ? j : i, horiz ? j + 1 : i - 1, horiz ? j - 1 : i + 1,
-                                                  horiz};
-                            x = walk_range<4>(g, max(k0[dir], kl + 1), maxd, horiz ? i : j, d,
-                                              horiz ? m.W - 1 : m.H - 1, zb, s, ca, cb);
-                        }
-                        rd[dir] = x != 0 ? x : -(maxd + 1);
+#pragma unroll
+                    for (int x = 0; x < NR; ++x) v[x] = line[x];
+                    line += hw;
+                } else if (inside) {  // 16-byte loads
+                    const float *row = m.t + ((int64_t)(valid ? A.j0 + oy + y : 0) * m.pitch + (valid ? A.i0 + ox : 0));
+#pragma unroll
+                    for (int x = 0; x < NR; x += 4) {
+                        const f32x4u q = gld4u(row + x);
+                        v[x] = canon(q.x);
+                        v[x + 1] = canon(q.y);
+                        v[x + 2] = canon(q.z);
+                        v[x + 3] = canon(q.w);
                     }
                 } else {
-                    rd[0] = walk_dir(m, i, j, zb, s, mk, maxd, -1, 0);
-                    rd[1] = walk_dir(m, i, j, zb, s, mk, maxd, 1, 0);
-                    rd[2] = walk_dir(m, i, j, zb, s, mk, maxd, 0, 1);
-                    rd[3] = walk_dir(m, i, j, zb, s, mk, maxd, 0, -1);
+                    const int gy = clampi(A.j0 + oy + y, m.H);
+                    const float *row = m.t + (int64_t)gy * m.pitch;
+#pragma unroll
+                    for (int x = 0; x < NR; ++x) v[x] = canon(gld(row + clampi(A.i0 + ox + x, m.W)));
                 }
-                const Axis axx = normalize_axis(rd[0], rd[1], s_ffx[L]);
-                const Axis axy = normalize_axis(rd[3], rd[2], s_ffy[L]);
-                s_val[e] = vis_rsmss(s, axx, axy);
+#pragma unroll
+                for (int x = NR - 1; x >= 0; --x) w = push_bit(w, v[x], A.zb);
+                any |= w;
+                every &= w;
+                *row_at(y) = (Word)w;
             }
-            __syncthreads();
-            // each fragment adds its own terms, in list order
-            const int e_lo = max(off, w0), e_hi = min(off + ne, w0 + cnt);
-            for (int e = e_lo; e < e_hi; ++e) acc += (double)s_val[e - w0];
         }
-        cm = c1;
-        c0 = c2;
-    }
-    if (valid) out[k] = (float)(acc / (double)((2 * r + 1) * (2 * r + 1)));
-}
+        __syncthreads();  // the band is free: column words overwrite it
+        // every test of each lane's window the same: its mean is its own test
+        const bool plain = !valid || any == 0u || every == kAll;
+        if (done || __ballot(!plain) == 0ull) {
+            plain_lit = done ? lit_all : any == 0u;
+            if (MULTI) lit_terms += plain_lit ? nx * ny : 0;
+            return true;
+        }
+        {
+            uint32_t a[S];
+#pragma unroll
+            for (int y = 0; y < S; ++y) a[y] = y < NR ? (uint32_t)*row_at(y) : 0u;
+            transpose_bits<S>(a);
+#pragma unroll
+            for (int x = 0; x < NR; ++x) {
+                const int q = x - k0;
+                if (q >= 0 && q < N) cw[q * 64] = (Word)a[x];
+            }
+        }
 
-// Radii up to this one stage the transposed band V (faster column words);
-// larger ones only H (half the LDS, more workgroups per CU).  Measured on the
-// 4K fenced frame, with V / without: r = 5 1.19 / 1.46 ms, 9 3.77 / 4.28,
-// 10 4.98 / 4.89, 13 8.43 / 7.25, 15 10.5 / 9.23 (before the kernel was held
-// to 128 VGPRs, which brought the H-only form to 4.32 / 6.38 / 8.78 ms at
-// r = 10 / 13 / 15).
-constexpr int kRpcfTransposedMaxR = 9;
+        const Word *const rwl = rw - lane - k0 * 64, *const cwl = cw - lane - k0 * 64;  // the wave's row, column 0
+        uint16_t *const list = reinterpret_cast<uint16_t *>(s_rcp + 2 * maxd + 2) + wave * list_cap;
+        uint16_t *const late = s_late[wave];
+        const lds_float *const rcp = (const lds_float *)s_rcp;
+        const bool map_32 = (int64_t)m.pitch * m.H <= (int64_t)(0xFFFFFFFFu / 4u);  // byte offsets fit 32 bits
+        // the lowest and the highest maxd bits of a word: the steps of a traversal
+        const uint32_t first = maxd < 32 ? (1u << (maxd & 31)) - 1u : ~0u;
+        const uint32_t last_bits = maxd < 32 ? ~(0xffffffffu >> (maxd & 31)) : ~0u;
+        // the value of listed term en = lane | x << 6 | y << 11; LATE: traversals
+        // that leave the window go on in global memory, else `leaves` is set.
+        // Every lane of the wave takes part (the fragments' values come by
+        // cross-lane reads).
+        auto term = [&](uint32_t en, auto late_tag, bool &leaves) -> float {
+            constexpr bool LATE = decltype(late_tag)::value;
+            const int L = en & 63u, x = (en >> 6) & 31u, y = en >> 11;
+            const Word *pr = rwl + y * 64 + L, *pc = cwl + x * 64 + L;
+            const uint32_t w = pr[0], wt = pr[64], wb = pr[-64];
+            const uint32_t c = pc[0], cl = pc[-64], cr = pc[64];
+            // all ones for a term in shadow: then bit 1 of a word means a test
+            // that differs from the term's
+            const uint32_t flip = (uint32_t)__builtin_amdgcn_sbfe((int)w, x, 1) & kAll;
+            const uint32_t dh = w ^ flip, dt = wt ^ flip, db = wb ^ flip, dv = c ^ flip, dl = cl ^ flip, dr = cr ^ flip;
+            // a step goes on where its texel's test is the term's and that of a
+            // side neighbour shared with the term's mask (Eq. 3) is not
+            const uint32_t mt = (uint32_t)__builtin_amdgcn_sbfe((int)dt, x, 1);
+            const uint32_t mb = (uint32_t)__builtin_amdgcn_sbfe((int)db, x, 1);
+            const uint32_t ml = (uint32_t)__builtin_amdgcn_sbfe((int)dl, y, 1);
+            const uint32_t mr = (uint32_t)__builtin_amdgcn_sbfe((int)dr, y, 1);
+            const uint32_t gh = ~dh & ((dt & mt) | (db & mb)), gv = ~dv & ((dl & ml) | (dr & mr));
+            bool leave[4];
+            auto up = [&](uint32_t go, uint32_t d, int p, bool &lv) {
+                WalkEnd e;
+                e.go = __builtin_ctz(~((go >> (p + 1)) & first));
+                e.end = __builtin_amdgcn_ubfe((d >> (p + 1)) & first, e.go, 1);
+                lv = p + e.go >= NR - 1 && e.go < maxd;
+                return e;
+            };
+            auto down = [&](uint32_t go, uint32_t d, int p, bool &lv) {
+                WalkEnd e;
+                e.go = __builtin_clz(~((go << (32 - p)) & last_bits));
+                e.end = (((d << (32 - p)) & last_bits) << e.go) >> 31;
+                lv = e.go >= p && e.go < maxd;
+                return e;
+            };
+            WalkEnd e0 = down(gh, dh, x, leave[0]), e1 = up(gh, dh, x, leave[1]);  // left, right
+            WalkEnd e2 = down(gv, dv, y, leave[2]), e3 = up(gv, dv, y, leave[3]);  // bottom, top
+            const bool s = flip == 0u;
+            if (!LATE) {
+                leaves = leave[0] | leave[1] | leave[2] | leave[3];
+            } else {
+                const int i = __shfl(A.i0, L) + ox + x, j = __shfl(A.j0, L) + oy + y;
+                const float zb = __shfl(A.zb, L);
+                uint32_t dirs = (leave[0] ? 1u : 0u) | (leave[1] ? 2u : 0u) |
+                                (leave[2] ? 4u : 0u) | (leave[3] ? 8u : 0u);
+                while (dirs != 0u) {  // each lane its next direction
+                    const int dir = __builtin_ctz(dirs);
+                    dirs &= dirs - 1u;
+                    const bool horiz = dir < 2;
+                    const int d = (dir & 1) ? 1 : -1, p0 = horiz ? i : j, pmax = (horiz ? m.W : m.H) - 1;
+                    const bool ca = (horiz ? mt : ml) != 0u, cb = (horiz ? mb : mr) != 0u;
+                    // the step that was found is the first outside the window
+                    const int k1 = 1 + (dir == 0 ? e0.go : dir == 1 ? e1.go : dir == 2 ? e2.go : e3.go);
+                    int q;
+                    if (map_32) {
+                        const unsigned pitch4 = 4u * (unsigned)m.pitch, fmul = horiz ? pitch4 : 4u;
+                        const int f = horiz ? j : i, fa = horiz ? j + 1 : i - 1, fb = horiz ? j - 1 : i + 1;
+                        const int nf = horiz ? m.H : m.W;
+                        const GlobalWalkReader g{(const char *)m.t, (unsigned)clampi(f, nf) * fmul,
+                                                 (unsigned)clampi(fa, nf) * fmul, (unsigned)clampi(fb, nf) * fmul,
+                                                 horiz ? 4u : pitch4};
+                        q = walk_range<4>(g, k1, maxd, p0, d, pmax, zb, s, ca, cb);
+                    } else {
+                        const MapLineReader g{m, horiz ? j : i, horiz ? j + 1 : i - 1, horiz ? j - 1 : i + 1, horiz};
+                        q = walk_range<4>(g, k1, maxd, p0, d, pmax, zb, s, ca, cb);
+                    }
+                    const WalkEnd e{q == 0 ? maxd : abs(q) - 1, q > 0 ? 1u : 0u};
+                    if (dir == 0) e0 = e;
+                    if (dir == 1) e1 = e;
+                    if (dir == 2) e2 = e;
+                    if (dir == 3) e3 = e;
+                }
+            }
+            const float tx = win_axis(e0, e1, __shfl(A.fx, L), rcp), ty = win_axis(e2, e3, __shfl(A.fy, L), rcp);
+            const float v = s ? (ty + tx) : ((1.0f - ty) - tx);
+            const float at0 = v > 0.0f ? v : 0.0f;
+            return at0 < 1.0f ? at0 : 1.0f;
+    };
+        auto add = [&](uint32_t en, float v) {
+            atomicAdd(&s_sum[wave * 64 + (en & 63u)], (unsigned long long)__double_as_longlong(1.0 + (double)v));
+    };
 
-// LDS texels for the staged bands of an RPCF workgroup: enough for a tile
-// whose texel footprint spans up to 13 x 17 texels, within 64 KiB with the
-// kernel's static LDS.
-inline int rpcf_cap(int r, int maxd) {
-    const int R = r + (maxd < kRpcfReach ? maxd : kRpcfReach);
-    const int want = r <= kRpcfTransposedMaxR
-                         ? (12 + 2 * R + 1) * (16 + 2 * r + 3) + (12 + 2 * r + 3) * ((16 + 2 * R + 1 + 7) | 1)
-                         : (12 + 2 * R + 1) * (16 + 2 * r + 3 + 7);
-    const int room = (65536 - 12288) / 4;
-    return want < room ? want : room;
-}
-
-inline void launch_rpcf(const MapView &mv, const float *frags, int64_t n, int64_t view_width, float bias, int maxd,
-                        int r, float *out, hipStream_t stream) {
-    if (r > kRpcfMaxR) {
-        hipLaunchKernelGGL(rpcf_naive_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, mv, frags,
-                           n, bias, maxd, r, out);
+        const uint32_t range = valid ? ((2u << (nx - 1)) - 1u) << c0 : 0u;  // the part's columns
+        const int y1 = c0 + ny - 1;
+        int listed = 0, n_late = 0;         // of the wave
+        int y = c0 - 1;
+        // rows y - 1, y, y + 1 and (on its way) y + 2
+        uint32_t wm = 0u, w = rw[(y - k0) * 64], wp = rw[(y - k0 + 1) * 64], wn = rw[(y - k0 + 2) * 64], bits = 0u;
+        auto below = [&](unsigned long long has) -> int {
+            return __builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
+    };
+        bool last = false;
+        while (!last) {
+            // list terms, each lane its next one, until a batch waits or the rows
+            // are through
+            do {
+                if (__ballot(bits != 0u) == 0ull) {
+                    if (y == y1) {
+                        last = true;
+                        break;
+                    }
+                    ++y;
+                    wm = w;
+                    w = wp;
+                    wp = wn;
+                    wn = rw[min(y + 2 - k0, N - 1) * 64];
+                    bits = ((w ^ (w << 1)) | (w ^ (w >> 1)) | (w ^ wm) | (w ^ wp)) & range;
+                    lit_terms += __builtin_popcount(~(bits | w) & range);
+                    edge_terms += __builtin_popcount(bits);
+                }
+                const unsigned long long has = __ballot(bits != 0u);
+                const uint32_t row = (uint32_t)lane | (uint32_t)y << 11;
+                if (bits != 0u) list[listed + below(has)] = (uint16_t)(row | (uint32_t)__builtin_ctz(bits) << 6);
+                listed += __builtin_popcountll(has);
+                bits &= bits - 1u;
+            } while (listed <= list_cap - 64);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // evaluate the full waves of terms (at the end: all of them)
+            const int todo = last ? listed : listed & ~63;
+            for (int e = 0; e < todo || (last && n_late > 0); e += 64) {
+                const bool on = e + lane < todo;
+                const uint32_t en = on ? list[e + lane] : (uint32_t)c0 * 0x840u;  // idle lanes: row and column c0
+                bool leaves = false;
+                const float v = term(en, std::false_type{}, leaves);
+                leaves = leaves && on;
+                if (on && !leaves) add(en, v);
+                const unsigned long long lv = __ballot(leaves);
+                if (leaves) late[n_late + below(lv)] = (uint16_t)en;
+                n_late += __builtin_popcountll(lv);
+                // the terms that left the window, a full wave of them at a time
+                while (n_late >= 64 || (last && e + 64 >= todo && n_late > 0)) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    // the newest ones, so that none is moved
+                    const int from = max(n_late - 64, 0);
+                    const bool lon = from + lane < n_late;
+                    const uint32_t el = late[lon ? from + lane : 0];
+                    bool unused;
+                    const float lval = term(el, std::true_type{}, unused);
+                    if (lon) add(el, lval);
+                    n_late = from;
+                }
+            }
+            const int left = listed - todo;
+            const uint16_t keep = lane < left ? list[todo + lane] : (uint16_t)0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane < left) list[lane] = keep;
+            listed = left;
+        }
+        return false;
+    };
+    bool plain_lit = false;
+    if (MULTI) {
+        for (int part = 0; part < parts * parts; ++part) (void)run_part(part, plain_lit);
+    } else if (run_part(0, plain_lit)) {
+        if (valid) out[k] = plain_lit ? 1.0f : 0.0f;
         return;
     }
-    const int cap = rpcf_cap(r, maxd);
-    const size_t lds = (size_t)cap * 4;
-    if (view_width > 0) {
-        constexpr int TW = 16, TH = kRpcfT / TW;
-        const int64_t rows = (n + view_width - 1) / view_width;
-        const int64_t tiles_x = (view_width + TW - 1) / TW;
-        const int64_t tiles = tiles_x * ((rows + TH - 1) / TH);
-        if (r <= kRpcfTransposedMaxR)
-            hipLaunchKernelGGL((rpcf_kernel<TW, true>), dim3((unsigned)tiles), dim3(kRpcfT), lds, stream, mv, frags,
-                               n, view_width, tiles_x, bias, maxd, r, cap, out);
-        else
-            hipLaunchKernelGGL((rpcf_kernel<TW, false>), dim3((unsigned)tiles), dim3(kRpcfT), lds, stream, mv, frags,
-                               n, view_width, tiles_x, bias, maxd, r, cap, out);
-    } else {
-        const int64_t tiles = (n + kRpcfT - 1) / kRpcfT;
-        if (r <= kRpcfTransposedMaxR)
-            hipLaunchKernelGGL((rpcf_kernel<kRpcfT, true>), dim3((unsigned)tiles), dim3(kRpcfT), lds, stream, mv,
-                               frags, n, n, tiles, bias, maxd, r, cap, out);
-        else
-            hipLaunchKernelGGL((rpcf_kernel<kRpcfT, false>), dim3((unsigned)tiles), dim3(kRpcfT), lds, stream, mv,
-                               frags, n, n, tiles, bias, maxd, r, cap, out);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (valid) {
+        const unsigned long long sum = s_sum[t] - (unsigned long long)edge_terms * 0x3ff0000000000000ull;
+        const double acc = (double)lit_terms + (double)sum * 0x1p-52;
+        out[k] = (float)(acc / (double)((2 * r + 1) * (2 * r + 1)));
+    }
+}
+
+// Launch of the window kernel: a band for a tile whose texel footprint spans up
+// to 17 x 17 texels (the column words' room where that is more), tiles dealt
+// to the XCDs in chunks of 32 (their cost varies with the edges; contiguous
+// ranges left XCDs idle: 4K r = 5 5-7% slower).  The list is as long as LDS
+// allows without losing a workgroup per CU: r = 13 fits five with 128 terms,
+// r = 14 never more than four.
+template <int NR, bool MULTI>
+void launch_window(const MapView &mv, const float *frags, int64_t n, int64_t view_width, float bias, int maxd, int r,
+                   int parts, float *out, hipStream_t stream) {
+    using Word = typename WinWord<NR>::T;
+    const int side = (2 * r + parts) / parts;  // terms a side of a part
+    const int N = NR <= 16 ? NR : side + 2;
+    const int words = 2 * N * 64 * (int)sizeof(Word), extra = (NR - N) * 64 * (int)sizeof(Word);  // bytes
+    const int band = std::max(words - 2 * extra, (NR + 16) * (NR + 16) * 4);
+    const int list = r == 13 ? 128 : (r == 14 ? 512 : 192);
+    const size_t lds = (size_t)(words + 2 * extra + band + 4 * (2 * maxd + 2) + 2 * 2 * list);
+    const int64_t vw = view_width > 0 ? view_width : n;
+    const int tw_log2 = view_width > 0 ? 4 : 7;  // 16 x 8 pixels, or 128 consecutive fragments
+    const int th = kRpcfT >> tw_log2;
+    const int64_t tiles_x = (vw + (1 << tw_log2) - 1) >> tw_log2;
+    const int64_t tiles = tiles_x * (((n + vw - 1) / vw + th - 1) / th);
+    constexpr int kChunkLog2 = 5;
+    hipLaunchKernelGGL((rpcf_window_kernel<NR, MULTI>), dim3((unsigned)tiles), dim3(kRpcfT), lds, stream, mv, frags, n,
+                       vw, tiles_x, tw_log2, bias, maxd, r, parts, side, band / 4, list, kChunkLog2, out);
+}
+
+// The window is 2r+3 rounded up to a multiple of 4 (of 2 measured slower up
+// to r = 6: fewer tests, but more traversals leave it).  Beyond r = 14 the box
+// goes in parts of at most 22 x 22 terms, whose 24 x 24 windows leave LDS for
+// 6 workgroups per CU; parts of 30 terms (32 x 32 windows) leave it for 4.
+inline void launch_rpcf(const MapView &mv, const float *frags, int64_t n, int64_t view_width, float bias, int maxd,
+                        int r, float *out, hipStream_t stream) {
+    if (r > kWinMaxR) {
+        const int parts = (2 * r + kWinPart) / kWinPart;  // of 2r+1 terms
+        launch_window<24, true>(mv, frags, n, view_width, bias, maxd, r, parts, out, stream);
+        return;
+    }
+    switch ((2 * r + 3 + 3) & ~3) {
+        case 8: launch_window<8, false>(mv, frags, n, view_width, bias, maxd, r, 1, out, stream); break;
+        case 12: launch_window<12, false>(mv, frags, n, view_width, bias, maxd, r, 1, out, stream); break;
+        case 16: launch_window<16, false>(mv, frags, n, view_width, bias, maxd, r, 1, out, stream); break;
+        case 20: launch_window<20, false>(mv, frags, n, view_width, bias, maxd, r, 1, out, stream); break;
+        case 24: launch_window<24, false>(mv, frags, n, view_width, bias, maxd, r, 1, out, stream); break;
+        case 28: launch_window<28, false>(mv, frags, n, view_width, bias, maxd, r, 1, out, stream); break;
+        default: launch_window<32, false>(mv, frags, n, view_width, bias, maxd, r, 1, out, stream); break;
     }
 }
 
