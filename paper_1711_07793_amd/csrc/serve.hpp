@@ -154,6 +154,72 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
                                                           J.mode == 0);
 }
 
+// A view's lights and its composite in one pass: a workgroup takes a screen
+// tile of the view through every light in turn, with the running sums of its
+// fragments in LDS, and stores the composite once.  The per-light results
+// reach memory only where the caller asked for them.
+struct ViewLight {
+    const float *t;  // map
+    const float *frags;
+    void *out;       // the caller's buffer, or null
+    int64_t pitch;
+    int32_t W, H;
+    float bias, w;
+    int16_t maxd;
+    uint8_t vec_ok, mode;
+};
+
+struct ViewJob {
+    float *out;      // composite
+    int32_t n, vw, tiles_x, first_light, n_lights, vec_out;
+};
+
+constexpr int kViewCap = 2016;  // staged texels: 7 workgroups per CU beside the sums
+constexpr int kArgViews = 20;
+constexpr int kArgViewLights = 40;
+
+struct ViewArgs {
+    int32_t n_jobs;
+    int64_t first[kArgViews];
+    ViewJob jobs[kArgViews];
+    ViewLight lights[kArgViewLights];
+};
+
+template <int TW>
+__global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(7, 7))) void serve_view_kernel(const ViewArgs a,
+                                                                                                   int apron, int cap) {
+    extern __shared__ float s_tex[];
+    __shared__ TileShared sh;
+    __shared__ float s_sum[kTileF];
+    const int64_t g = xcd_chunked(blockIdx.x, gridDim.x, kServeChunkLog2);
+    const int j = find_job(a.first, a.n_jobs, g);
+    const ViewJob &J = a.jobs[j];
+    const int64_t tile = g - a.first[j];
+    for (int l = 0; l < J.n_lights; ++l) {
+        const ViewLight &L = a.lights[J.first_light + l];
+        MapView m;
+        m.t = L.t;
+        m.pitch = L.pitch;
+        m.W = L.W;
+        m.H = L.H;
+        const TilePos<TW, int> P(J.vw, J.n, J.tiles_x, tile, opaque_tid());
+        float fr[3 * kF];
+        load_tile_frags<TW>(L.frags, P, L.vec_ok, fr);
+        process_tile_loaded<2, TW, kWalkFirst, kWalkSteps, true, true>(m, L.frags, J.vw, L.bias, L.maxd, apron, cap,
+                                                                       L.vec_ok, L.out, P, fr, sh, s_tex, L.mode == 0,
+                                                                       NoPrefetch{}, TileSum{s_sum, L.w, l == 0});
+    }
+    __syncthreads();
+    const int t = opaque_tid();
+    const TilePos<TW, int> P(J.vw, J.n, J.tiles_x, tile, t);
+    const lds_float *v = (const lds_float *)s_sum + kF * t;
+    if (J.vec_out && P.avail == kF) {
+        gst4(reinterpret_cast<float4 *>(at(J.out, P.k0)), make_float4(v[0], v[1], v[2], v[3]));
+    } else {
+        for (int f = 0; f < P.avail; ++f) gst(at(J.out, P.k0 + f), v[f]);
+    }
+}
+
 }  // namespace rbsm
 
 // ---------------------------------------------------------------------------
@@ -213,6 +279,17 @@ int64_t request_work(const EngineReq &R) {
     for (int l = 0; l < r.n_lights; ++l) b += r.n * (12 + (r.lights[l].mode == 0 ? 1 : 4));
     if (r.composite) b += r.n * 4;
     return b;
+}
+
+// Can the request's lights and composite run as one job of the view kernel?
+// A composite is wanted, every light's pass is the tile pass (no RPCF), and
+// the view fits the 32-bit index form.
+bool is_view_job(const EngineReq &R) {
+    const rbsm_request &q = R.req;
+    if (!R.d_comp || q.n == 0) return false;
+    for (int l = 0; l < q.n_lights; ++l)
+        if (q.lights[l].kernel_radius > 0) return false;
+    return rbsm::index32(q.n, job_layout(q.n, q.view_width, rbsm::kServeTileW).vw, rbsm::kServeTileW);
 }
 
 // Is p device memory of `device` (so kernels may write it in place)?
@@ -307,6 +384,7 @@ bool rbsm_engine::step_launch() {
     std::vector<EngineReq *> batch;
     std::vector<std::pair<EngineReq *, int>> rpcf_jobs, tile_jobs;  // (request, light)
     std::vector<rbsm::CompJob> comps;
+    std::vector<EngineReq *> views;  // requests whose lights and composite are one job of the view kernel
     int n_jobs = 0;
     size_t taken = 0;
     for (; taken < admitted.size(); ++taken) {
@@ -314,6 +392,11 @@ bool rbsm_engine::step_launch() {
         const rbsm_request &q = R->req;
         if (n_jobs + q.n_lights > rbsm::kServeMaxJobs || (int)batch.size() >= rbsm::kServeMaxReqs) break;
         n_jobs += q.n_lights;
+        batch.push_back(R);
+        if (is_view_job(*R)) {
+            views.push_back(R);
+            continue;
+        }
         for (int l = 0; l < q.n_lights; ++l) {
             if (q.lights[l].kernel_radius > 0) rpcf_jobs.push_back({R, l});
             else tile_jobs.push_back({R, l});
@@ -330,7 +413,6 @@ bool rbsm_engine::step_launch() {
             }
             comps.push_back(C);
         }
-        batch.push_back(R);
     }
     if (batch.empty()) return false;
     admitted.erase(admitted.begin(), admitted.begin() + taken);
@@ -343,6 +425,46 @@ bool rbsm_engine::step_launch() {
     }
     if (e == hipSuccess) e = hipEventRecord(S.compute_start, s_compute);
     const size_t lds = (size_t)kDefaultTile.cap * sizeof(float);
+    // view jobs, in chunks that fit the kernel arguments
+    for (size_t c = 0; c < views.size() && e == hipSuccess;) {
+        rbsm::ViewArgs A{};
+        int64_t tiles = 0;
+        int lights = 0;
+        for (; c < views.size() && A.n_jobs < rbsm::kArgViews; ++c) {
+            const EngineReq *R = views[c];
+            const rbsm_request &q = R->req;
+            if (lights + q.n_lights > rbsm::kArgViewLights) break;
+            const JobLayout lay = job_layout(q.n, q.view_width, rbsm::kServeTileW);
+            rbsm::ViewJob &J = A.jobs[A.n_jobs];
+            J.out = R->d_comp;
+            J.n = (int32_t)q.n;
+            J.vw = (int32_t)lay.vw;
+            J.tiles_x = (int32_t)lay.tiles_x;
+            J.first_light = lights;
+            J.n_lights = q.n_lights;
+            J.vec_out = (uintptr_t)J.out % 16 == 0 && lay.vw % 4 == 0;
+            for (int l = 0; l < q.n_lights; ++l) {
+                const rbsm_request_light &L = q.lights[l];
+                rbsm::ViewLight &V = A.lights[lights++];
+                V.t = R->maps[l].t;
+                V.pitch = R->maps[l].pitch;
+                V.W = R->maps[l].W;
+                V.H = R->maps[l].H;
+                V.frags = R->d_frags[l];
+                V.out = L.out ? R->d_out[l] : nullptr;
+                V.bias = L.depth_bias;
+                V.w = L.weight;
+                V.maxd = (int16_t)L.max_dist;
+                V.mode = (uint8_t)L.mode;
+                V.vec_ok = ((uintptr_t)V.frags % 16 == 0) && ((uintptr_t)V.out % (L.mode == 0 ? 4 : 16) == 0) &&
+                           (lay.vw % 4 == 0);
+            }
+            A.first[A.n_jobs++] = tiles;
+            tiles += lay.tiles;
+        }
+        hipLaunchKernelGGL(rbsm::serve_view_kernel<rbsm::kServeTileW>, dim3((unsigned)tiles), dim3(kT),
+                           rbsm::kViewCap * sizeof(float), s_compute, A, kDefaultTile.apron, rbsm::kViewCap);
+    }
     // tile jobs of both modes, in chunks that fit the kernel arguments
     {
         const auto &list = tile_jobs;

@@ -360,6 +360,18 @@ __device__ __forceinline__ void load_tile_frags(const float *__restrict__ frags,
     }
 }
 
+// Weighted sums of a tile's results over several passes: one float per
+// fragment in LDS, started by the first pass.
+struct TileSum {
+    float *v;
+    float w;
+    bool first;
+    __device__ __forceinline__ void add(int slot, float x) const {
+        lds_float *p = (lds_float *)v + slot;
+        *p = (first ? 0.0f : *p) + w * x;
+    }
+};
+
 struct NoPrefetch {
     __device__ __forceinline__ void operator()() const {}
 };
@@ -385,13 +397,18 @@ struct NoPrefetch {
 // read from and by which lane: every result equals the per-fragment listing.
 // MODE: 1 hard pass, 0 RSMSS, 2 either, chosen per call by hard_rt (one code
 // path for workgroups of both modes in one launch).
-template <int MODE, int TW, int WF = kWalkFirst, int WB = kWalkSteps, bool LW = false, class Prefetch = NoPrefetch,
-          class IX>
+// SUM: besides (out_v may be null), every result times sum.w is added to the
+// tile's running sums in LDS; tiles of one sum follow each other in a
+// workgroup without a barrier of their own (a tile's first barrier comes
+// before it reads or writes what the last one may still use).
+template <int MODE, int TW, int WF = kWalkFirst, int WB = kWalkSteps, bool LW = false, bool SUM = false,
+          class Prefetch = NoPrefetch, class IX>
 __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__restrict__ frags, int64_t vw64,
                                                     float bias, int maxd, int apron,
                                                     int cap, int vec_ok, void *__restrict__ out_v,
                                                     const TilePos<TW, IX> &P, const float (&fr)[3 * kF], TileShared &sh,
-                                                    float *s_tex, bool hard_rt, const Prefetch &prefetch) {
+                                                    float *s_tex, bool hard_rt, const Prefetch &prefetch,
+                                                    const TileSum &sum = TileSum{}) {
     const bool HARD = MODE == 2 ? hard_rt : MODE == 1;
     constexpr int TH = kTileF / TW;
     constexpr int LPR = TW / kF;
@@ -582,7 +599,14 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
 
         // final results of every fragment that is not an edge fragment
         const bool any_edge = edge[0] | edge[1] | edge[2] | edge[3];
-        if (HARD) {
+        if constexpr (SUM) {
+#pragma unroll
+            for (int f = 0; f < kF; ++f)
+                if (!edge[f]) sum.add(kF * t + f, s[f] ? 1.0f : 0.0f);
+        }
+        if (SUM && out_v == nullptr) {
+            // the sums alone
+        } else if (HARD) {
             uint8_t *out = static_cast<uint8_t *>(out_v);
             if (full && !any_edge) {
                 uint32_t packed = 0;
@@ -829,6 +853,11 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
         const bool s = (q_sm[e] & 16u) != 0;
         const Axis axx = normalize_axis(q_rd[e][0], q_rd[e][1], fx);
         const Axis axy = normalize_axis(q_rd[e][3], q_rd[e][2], fy);
+        if constexpr (SUM) {
+            const float v = HARD ? vis_hard(axx, axy) : vis_rsmss(s, axx, axy);
+            sum.add(q_slot[e], v);
+            if (out_v == nullptr) continue;
+        }
         if (HARD) gst(at(static_cast<uint8_t *>(out_v), k), (uint8_t)(vis_hard(axx, axy) != 0.0f ? 1 : 0));
         else gst(at(static_cast<float *>(out_v), k), vis_rsmss(s, axx, axy));
     }
