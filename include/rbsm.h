@@ -65,7 +65,7 @@ typedef struct {
                                k / view_width); the last row may be partial), so
                                the pass can work in 2-D screen tiles whose
                                light-space footprint is staged in LDS; 0 = no
-                               layout (flat chunks) */
+                               layout (a list) */
 } rbsm_params;
 
 /*
@@ -131,7 +131,7 @@ int rbsm_footprint(const float *shadow_map, const float *frags, int64_t n, const
  */
 typedef struct {
     int32_t tile_w;     /* screen-tile width in pixels: 16, 32 or 64 (height 1024 / tile_w);
-                           ignored (flat 1024-fragment chunks) when view_width is 0 */
+                           ignored by the single-pass entry points when view_width is 0 */
     int32_t apron;      /* texels staged around the tile's texel box, 1..8 */
     int32_t lds_cap;    /* LDS texel capacity per workgroup, 256..12288, or 0:
                            nothing staged, every texel read from global memory */

@@ -241,8 +241,7 @@ bool make_args(const HostTables &T, BatchArgs *a) {
         A.tile_base = (int32_t)D.tile_base;
         A.bias = D.bias;
         A.maxd = (int16_t)D.maxd;
-        A.vec_ok = (uint8_t)D.vec_ok;
-        A.mode = (uint8_t)D.mode;
+        A.mode = (int16_t)D.mode;
         a->first[k] = (int32_t)D.tile_base;
         ++k;
     }
@@ -294,8 +293,6 @@ int make_tables(const char *fn, const rbsm_job *jobs, int32_t n_jobs, int tile_w
         D.bias = J.params.depth_bias;
         D.maxd = J.params.max_dist;
         D.mode = J.mode;
-        D.vec_ok = ((uintptr_t)J.frags % 16 == 0) && ((uintptr_t)J.out % (J.mode == 0 ? 4 : 16) == 0) &&
-                   (L.vw % 4 == 0);
         T.job_tiles[j] = L.tiles;
         frags += J.n;
     }
@@ -585,7 +582,7 @@ int rbsm_visibility(const float *shadow_map, const float *frags, int64_t n, cons
     const int st = validate("rbsm_visibility", shadow_map, frags, n, p, out_mask, 1, false, &mv);
     if (st != RBSM_OK) return st;
     if (n == 0) return RBSM_OK;
-    launch_pass<true>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, kDefaultTile, out_mask, 4, stream);
+    launch_pass<true>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, kDefaultTile, out_mask, stream);
     return launched("rbsm_visibility");
 }
 
@@ -597,7 +594,7 @@ int rsmss_visibility(const float *shadow_map, const float *frags, int64_t n, con
     if (n == 0) return RBSM_OK;
     const int r = p->kernel_radius;
     if (r == 0) {
-        launch_pass<false>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, kDefaultTile, out_vis, 16,
+        launch_pass<false>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, kDefaultTile, out_vis,
                            stream);
     } else {
         launch_rpcf(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, r, out_vis, stream);
@@ -664,9 +661,9 @@ int rbsm_pass_tuned(int32_t mode, const float *shadow_map, const float *frags, i
     if (n == 0) return RBSM_OK;
     const TileConfig cfg{tune->tile_w, tune->apron, tune->lds_cap, tune->persistent, tune->xcd_chunk};
     if (mode == 0)
-        launch_pass<true>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, cfg, out, 4, stream);
+        launch_pass<true>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, cfg, out, stream);
     else
-        launch_pass<false>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, cfg, out, 16, stream);
+        launch_pass<false>(mv, frags, n, p->view_width, p->depth_bias, p->max_dist, cfg, out, stream);
     return launched("rbsm_pass_tuned");
 }
 

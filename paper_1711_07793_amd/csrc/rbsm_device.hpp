@@ -45,17 +45,15 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ f32x4u gld4u(const float *p) {
     return *(const __attribute__((address_space(1))) f32x4u *)p;
 }
-// 16-byte forms through a native vector type (HIP's float4 is a class whose
-// copy takes a generic reference, which would bring the flat access back).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 gld4(const float4 *p) {
-    const f32x4 v = *(const __attribute__((address_space(1))) f32x4 *)p;
-    return make_float4(v.x, v.y, v.z, v.w);
+// 16-byte store of four floats at 4-byte alignment, 4-byte store at any.
+__device__ __forceinline__ void gst4u(float *p, float x, float y, float z, float w) {
+    f32x4u v;
+    v.x = x; v.y = y; v.z = z; v.w = w;
+    *(__attribute__((address_space(1))) f32x4u *)p = v;
 }
-__device__ __forceinline__ void gst4(float4 *p, float4 v) {
-    f32x4 w;
-    w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
-    *(__attribute__((address_space(1))) f32x4 *)p = w;
+typedef uint32_t u32u __attribute__((aligned(1)));
+__device__ __forceinline__ void gst_u32(uint8_t *p, uint32_t v) {
+    *(__attribute__((address_space(1))) u32u *)p = v;
 }
 
 // Nearest-texel fetch with clamp-to-edge.
@@ -88,59 +86,6 @@ __device__ __forceinline__ Addr address(float u, float v, float z, int W, int H,
     a.j0 = (int)fminf(fmaxf(fly, -1048576.0f), 1048576.0f);
     a.zb = z - bias;
     return a;
-}
-
-// Bounded traversal along (DX, DY) (Listing 3 with the shared-direction test
-// of Sec. 3.1.3).  Returns +k when the k-th texel has the opposite test (an
-// edge end), -k when the k-th texel stops sharing a discontinuity direction
-// with the fragment, -(maxd + 1) when the walk runs out.
-//
-// Only discontinuity bits perpendicular to the walk can be shared: the texel
-// behind a visited texel has the fragment's test result, and a fragment with a
-// discontinuity in the walking direction ends its walk at k = 1.  So a step
-// reads the visited texel and at most its two perpendicular neighbours, and
-// only those whose bit is set in the fragment's mask m0.
-template <int DX, int DY>
-__device__ __forceinline__ int walk(const MapView &m, int i0, int j0, float zb, bool s, unsigned m0,
-                                    int maxd) {
-    const bool chk_a = DX != 0 ? (m0 & BIT_T) != 0 : (m0 & BIT_L) != 0;
-    const bool chk_b = DX != 0 ? (m0 & BIT_B) != 0 : (m0 & BIT_R) != 0;
-    int i = i0, j = j0;
-    for (int k = 1; k <= maxd; ++k) {
-        i += DX;
-        j += DY;
-        if (lit(zb, texel(m, i, j)) != s) return k;
-        bool share = false;
-        if (chk_a) share |= lit(zb, DX != 0 ? texel(m, i, j + 1) : texel(m, i - 1, j)) != s;
-        if (chk_b) share |= lit(zb, DX != 0 ? texel(m, i, j - 1) : texel(m, i + 1, j)) != s;
-        if (!share) return -k;
-    }
-    return -(maxd + 1);
-}
-
-// The same traversal with the direction as a run-time value, so lanes that
-// walk different directions of different fragments share one instruction
-// stream.  (dx, dy) is one of (-1,0), (1,0), (0,1), (0,-1).
-__device__ __forceinline__ int walk_dir(const MapView &m, int i0, int j0, float zb, bool s, unsigned m0,
-                                        int maxd, int dx, int dy) {
-    const bool horiz = dx != 0;
-    const bool chk_a = horiz ? (m0 & BIT_T) != 0 : (m0 & BIT_L) != 0;
-    const bool chk_b = horiz ? (m0 & BIT_B) != 0 : (m0 & BIT_R) != 0;
-    // offsets of the two perpendicular neighbours: top/bottom or left/right
-    const int ax = horiz ? 0 : -1, ay = horiz ? 1 : 0;
-    const int bx = horiz ? 0 : 1, by = horiz ? -1 : 0;
-    int i = i0, j = j0;
-    for (int k = 1; k <= maxd; ++k) {
-        i += dx;
-        j += dy;
-        const float tc = texel(m, i, j);
-        const float ta = texel(m, i + ax, j + ay);
-        const float tb = texel(m, i + bx, j + by);
-        if (lit(zb, tc) != s) return k;
-        const bool share = (chk_a && lit(zb, ta) != s) || (chk_b && lit(zb, tb) != s);
-        if (!share) return -k;
-    }
-    return -(maxd + 1);
 }
 
 // One axis of the normalized discontinuity space (Eq. 5): the code counts the
@@ -182,34 +127,6 @@ __device__ __forceinline__ float vis_rsmss(bool s, Axis x, Axis y) {
     const float v = s ? (ty + tx) : ((1.0f - ty) - tx);
     const float lo = v > 0.0f ? v : 0.0f;
     return lo < 1.0f ? lo : 1.0f;
-}
-
-// Discontinuity mask of texel (i, j) at depth zb, given its own test s.
-__device__ __forceinline__ unsigned mask_of(const MapView &m, int i, int j, float zb, bool s) {
-    unsigned b = 0;
-    b |= (lit(zb, texel(m, i - 1, j)) != s) ? BIT_L : 0u;
-    b |= (lit(zb, texel(m, i + 1, j)) != s) ? BIT_R : 0u;
-    b |= (lit(zb, texel(m, i, j + 1)) != s) ? BIT_T : 0u;
-    b |= (lit(zb, texel(m, i, j - 1)) != s) ? BIT_B : 0u;
-    return b;
-}
-
-// Visibility of a fragment whose texel is (i0, j0): Listing 1 with the
-// hard (HARD) or filtering visibility function.
-template <bool HARD>
-__device__ __forceinline__ float eval_texel(const MapView &m, int i0, int j0, float fx, float fy,
-                                            float zb, int maxd) {
-    const bool s = lit(zb, texel(m, i0, j0));
-    if (HARD && !s) return 0.0f;
-    const unsigned m0 = mask_of(m, i0, j0, zb, s);
-    if (m0 == 0u) return s ? 1.0f : 0.0f;
-    const int rl = walk<-1, 0>(m, i0, j0, zb, s, m0, maxd);
-    const int rr = walk<+1, 0>(m, i0, j0, zb, s, m0, maxd);
-    const int rt = walk<0, +1>(m, i0, j0, zb, s, m0, maxd);
-    const int rb = walk<0, -1>(m, i0, j0, zb, s, m0, maxd);
-    const Axis ax = normalize_axis(rl, rr, fx);
-    const Axis ay = normalize_axis(rb, rt, fy);
-    return HARD ? vis_hard(ax, ay) : vis_rsmss(s, ax, ay);
 }
 
 }  // namespace rbsm

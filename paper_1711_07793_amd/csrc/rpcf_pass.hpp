@@ -49,19 +49,6 @@ __device__ __forceinline__ uint32_t push_bit(uint32_t w, float t, float zb) {
 
 __device__ __forceinline__ float canon(float t) { return t != t ? __builtin_inff() : t + 0.0f; }
 
-// A map line and its two side lines (rows c, a, b when horizontal, columns
-// when not), read from global memory with clamp-to-edge.
-struct MapLineReader {
-    MapView m;
-    int c, a, b;
-    bool horiz;
-    __device__ __forceinline__ void operator()(int p, float &tc, float &ta, float &tb) const {
-        tc = horiz ? texel(m, p, c) : texel(m, c, p);
-        ta = horiz ? texel(m, p, a) : texel(m, a, p);
-        tb = horiz ? texel(m, p, b) : texel(m, b, p);
-    }
-};
-
 // A word of NR bits.
 template <int NR>
 struct WinWord {

@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     const int j = find_job(a.first, a.n_jobs, g);
     const JobDev &J = a.jobs[j];
     process_tile<2, TW, kWalkFirst, kWalkSteps, IX, true>(J.m, J.frags, J.n, J.vw, J.tiles_x, J.bias, J.maxd, apron,
-                                                          cap, J.vec_ok, J.out, g - a.first[j], sh, s_tex,
+                                                          cap, J.out, g - a.first[j], sh, s_tex,
                                                           J.mode == 0);
 }
 
@@ -166,12 +166,12 @@ struct ViewLight {
     int32_t W, H;
     float bias, w;
     int16_t maxd;
-    uint8_t vec_ok, mode;
+    int16_t mode;
 };
 
 struct ViewJob {
     float *out;      // composite
-    int32_t n, vw, tiles_x, first_light, n_lights, vec_out;
+    int32_t n, vw, tiles_x, first_light, n_lights;
 };
 
 constexpr int kViewCap = 2016;  // staged texels: 7 workgroups per CU beside the sums
@@ -204,17 +204,17 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(7, 7))) void
         m.H = L.H;
         const TilePos<TW, int> P(J.vw, J.n, J.tiles_x, tile, opaque_tid());
         float fr[3 * kF];
-        load_tile_frags<TW>(L.frags, P, L.vec_ok, fr);
+        load_tile_frags<TW>(L.frags, J.n, P, fr);
         process_tile_loaded<2, TW, kWalkFirst, kWalkSteps, true, true>(m, L.frags, J.vw, L.bias, L.maxd, apron, cap,
-                                                                       L.vec_ok, L.out, P, fr, sh, s_tex, L.mode == 0,
+                                                                       L.out, P, fr, sh, s_tex, L.mode == 0,
                                                                        NoPrefetch{}, TileSum{s_sum, L.w, l == 0});
     }
     __syncthreads();
     const int t = opaque_tid();
     const TilePos<TW, int> P(J.vw, J.n, J.tiles_x, tile, t);
     const lds_float *v = (const lds_float *)s_sum + kF * t;
-    if (J.vec_out && P.avail == kF) {
-        gst4(reinterpret_cast<float4 *>(at(J.out, P.k0)), make_float4(v[0], v[1], v[2], v[3]));
+    if (P.avail == kF) {
+        gst4u(at(J.out, P.k0), v[0], v[1], v[2], v[3]);
     } else {
         for (int f = 0; f < P.avail; ++f) gst(at(J.out, P.k0 + f), v[f]);
     }
@@ -442,7 +442,6 @@ bool rbsm_engine::step_launch() {
             J.tiles_x = (int32_t)lay.tiles_x;
             J.first_light = lights;
             J.n_lights = q.n_lights;
-            J.vec_out = (uintptr_t)J.out % 16 == 0 && lay.vw % 4 == 0;
             for (int l = 0; l < q.n_lights; ++l) {
                 const rbsm_request_light &L = q.lights[l];
                 rbsm::ViewLight &V = A.lights[lights++];
@@ -455,9 +454,7 @@ bool rbsm_engine::step_launch() {
                 V.bias = L.depth_bias;
                 V.w = L.weight;
                 V.maxd = (int16_t)L.max_dist;
-                V.mode = (uint8_t)L.mode;
-                V.vec_ok = ((uintptr_t)V.frags % 16 == 0) && ((uintptr_t)V.out % (L.mode == 0 ? 4 : 16) == 0) &&
-                           (lay.vw % 4 == 0);
+                V.mode = (int16_t)L.mode;
             }
             A.first[A.n_jobs++] = tiles;
             tiles += lay.tiles;
@@ -489,8 +486,6 @@ bool rbsm_engine::step_launch() {
                 D.bias = L.depth_bias;
                 D.maxd = L.max_dist;
                 D.mode = L.mode;
-                D.vec_ok = ((uintptr_t)D.frags % 16 == 0) && ((uintptr_t)D.out % (L.mode == 0 ? 4 : 16) == 0) &&
-                           (lay.vw % 4 == 0);
                 ix32 = ix32 && rbsm::index32(q.n, lay.vw, rbsm::kServeTileW);
                 A.first[A.n_jobs++] = tiles;
                 tiles += lay.tiles;

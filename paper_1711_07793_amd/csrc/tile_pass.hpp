@@ -201,6 +201,19 @@ struct GlobalWalkReader {  // a map under 4 GiB in global memory
     }
 };
 
+// A map line of any map and its two side lines (rows c, a, b when horizontal, columns
+// when not), read from global memory with clamp-to-edge.
+struct MapLineReader {
+    MapView m;
+    int c, a, b;
+    bool horiz;
+    __device__ __forceinline__ void operator()(int p, float &tc, float &ta, float &tb) const {
+        tc = horiz ? texel(m, p, c) : texel(m, c, p);
+        ta = horiz ? texel(m, p, a) : texel(m, a, p);
+        tb = horiz ? texel(m, p, b) : texel(m, b, p);
+    }
+};
+
 struct LdsWalkReader {  // the staged window in LDS (row stride bw)
     const lds_float *t;   // window base
     int c, a, b;          // window index of the fixed coordinate, less the moving one's origin
@@ -306,8 +319,7 @@ __device__ __forceinline__ T *at(T *p, IX k) {
 }
 
 // Where a thread's 4 pixels of tile `tile_id` sit: a TW x (1024/TW) tile of a
-// row-major image of width vw (flat mode: vw = n, TW = 1024), each thread 4
-// consecutive pixels of one row.  Tile and image counts stay below 2^31.
+// row-major image of width vw, each thread 4 consecutive pixels of one row.  Tile and image counts stay below 2^31.
 // IX = int: the caller has checked index32.  IX = int64_t: when every index
 // is below 2^31 (a uniform test) the per-thread arithmetic is still 32-bit.
 template <int TW, class IX = int64_t>
@@ -335,27 +347,37 @@ struct TilePos {
 };
 
 // Fragment loads of one thread for one tile: one 48-byte load (three 16-byte
-// ones) when the 4 pixels are in range and aligned, else guarded 4-byte loads
-// (zeros where a pixel lies outside the image).
+// ones, dword aligned: rows and lists of any length start anywhere).  A
+// thread whose pixels run past a row's end reads the next row's with it; past
+// the last fragment it reads the last four, shifted into place.  Values of
+// pixels outside the image are never used.  Fewer than four fragments are read
+// one by one.
 template <int TW, class IX>
-__device__ __forceinline__ void load_tile_frags(const float *__restrict__ frags, const TilePos<TW, IX> &P, int vec_ok,
+__device__ __forceinline__ void load_tile_frags(const float *__restrict__ frags, int64_t n, const TilePos<TW, IX> &P,
                                                 float (&fr)[3 * kF]) {
-    bool valid[kF];
-#pragma unroll
-    for (int f = 0; f < kF; ++f) valid[f] = f < P.avail;
-    if (vec_ok && valid[kF - 1]) {
-        const float4 *p4 = reinterpret_cast<const float4 *>(at(frags, 3 * P.k0));
-        const float4 a = gld4(p4), b = gld4(p4 + 1), c = gld4(p4 + 2);
+    const IX last = (IX)n - kF;
+    const IX k = P.k0 < last ? P.k0 : last;
+    if (last >= 0) {
+        const float *p = at(frags, 3 * k);
+        const f32x4u a = gld4u(p), b = gld4u(p + 4), c = gld4u(p + 8);
         fr[0] = a.x; fr[1] = a.y; fr[2] = a.z; fr[3] = a.w;
         fr[4] = b.x; fr[5] = b.y; fr[6] = b.z; fr[7] = b.w;
         fr[8] = c.x; fr[9] = c.y; fr[10] = c.z; fr[11] = c.w;
+        if (P.k0 > k) {
+#pragma unroll
+            for (int s = 0; s < kF - 1; ++s)
+                if (P.k0 - k > s) {
+#pragma unroll
+                    for (int q = 0; q < 3 * (kF - 1); ++q) fr[q] = fr[q + 3];
+                }
+        }
     } else {
 #pragma unroll
         for (int f = 0; f < kF; ++f) {
-            const IX k3 = 3 * (P.k0 + f);
-            fr[3 * f + 0] = valid[f] ? gld(at(frags, k3 + 0)) : 0.0f;
-            fr[3 * f + 1] = valid[f] ? gld(at(frags, k3 + 1)) : 0.0f;
-            fr[3 * f + 2] = valid[f] ? gld(at(frags, k3 + 2)) : 0.0f;
+            const IX k3 = f < P.avail ? 3 * (P.k0 + f) : 0;
+            fr[3 * f + 0] = gld(at(frags, k3));
+            fr[3 * f + 1] = gld(at(frags, k3 + 1));
+            fr[3 * f + 2] = gld(at(frags, k3 + 2));
         }
     }
 }
@@ -405,7 +427,7 @@ template <int MODE, int TW, int WF = kWalkFirst, int WB = kWalkSteps, bool LW = 
           class Prefetch = NoPrefetch, class IX>
 __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__restrict__ frags, int64_t vw64,
                                                     float bias, int maxd, int apron,
-                                                    int cap, int vec_ok, void *__restrict__ out_v,
+                                                    int cap, void *__restrict__ out_v,
                                                     const TilePos<TW, IX> &P, const float (&fr)[3 * kF], TileShared &sh,
                                                     float *s_tex, bool hard_rt, const Prefetch &prefetch,
                                                     const TileSum &sum = TileSum{}) {
@@ -431,7 +453,7 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
         bool valid[kF];
 #pragma unroll
         for (int f = 0; f < kF; ++f) valid[f] = f < P.avail;
-        const bool full = vec_ok && valid[kF - 1];
+        const bool full = valid[kF - 1];
 
         // cap == 0: direct reads, no box and no staging.  The queue counters
         // are cleared before the first fragment value is used, so the
@@ -612,7 +634,7 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
                 uint32_t packed = 0;
 #pragma unroll
                 for (int f = 0; f < kF; ++f) packed |= (uint32_t)(s[f] ? 1u : 0u) << (8 * f);
-                gst(reinterpret_cast<uint32_t *>(at(out, k0)), packed);
+                gst_u32(at(out, k0), packed);
             } else {
 #pragma unroll
                 for (int f = 0; f < kF; ++f)
@@ -621,8 +643,7 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
         } else {
             float *out = static_cast<float *>(out_v);
             if (full && !any_edge) {
-                gst4(reinterpret_cast<float4 *>(at(out, k0)),
-                    make_float4(s[0] ? 1.0f : 0.0f, s[1] ? 1.0f : 0.0f, s[2] ? 1.0f : 0.0f, s[3] ? 1.0f : 0.0f));
+                gst4u(at(out, k0), s[0] ? 1.0f : 0.0f, s[1] ? 1.0f : 0.0f, s[2] ? 1.0f : 0.0f, s[3] ? 1.0f : 0.0f);
             } else {
 #pragma unroll
                 for (int f = 0; f < kF; ++f)
@@ -874,13 +895,13 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
 template <int MODE, int TW, int WF = kWalkFirst, int WB = kWalkSteps, class IX = int64_t, bool LW = false>
 __device__ __forceinline__ void process_tile(MapView m, const float *__restrict__ frags, int64_t n, int64_t vw,
                                              int64_t tiles_x, float bias, int maxd, int apron, int cap,
-                                             int vec_ok, void *__restrict__ out_v, int64_t tile_id,
+                                             void *__restrict__ out_v, int64_t tile_id,
                                              TileShared &sh, float *s_tex, bool hard_rt = false) {
     // the tile's pixel positions, computed once for the loads and the pass
     const TilePos<TW, IX> P(vw, n, tiles_x, tile_id, opaque_tid());
     float fr[3 * kF];
-    load_tile_frags<TW>(frags, P, vec_ok, fr);
-    process_tile_loaded<MODE, TW, WF, WB, LW>(m, frags, vw, bias, maxd, apron, cap, vec_ok, out_v, P, fr, sh, s_tex,
+    load_tile_frags<TW>(frags, n, P, fr);
+    process_tile_loaded<MODE, TW, WF, WB, LW>(m, frags, vw, bias, maxd, apron, cap, out_v, P, fr, sh, s_tex,
                                               hard_rt, NoPrefetch{});
 }
 
@@ -892,7 +913,7 @@ struct JobDev {
     void *out;
     int64_t n, vw, tiles_x, tile_base;
     float bias;
-    int maxd, vec_ok, mode;  // mode 0 hard, 1 RSMSS
+    int maxd, mode;  // mode 0 hard, 1 RSMSS
 };
 
 // Persistent loop: the workgroup takes tiles g, g + G, g + 2G, ... of the
@@ -909,7 +930,7 @@ __device__ __forceinline__ void persistent_loop(const JobOf &job_of, int64_t til
     if (g >= tiles) return;
     JobDev J = job_of(g);
     float fr[3 * kF];
-    load_tile_frags<TW>(J.frags, TilePos<TW>(J.vw, J.n, J.tiles_x, g - J.tile_base, opaque_tid()), J.vec_ok, fr);
+    load_tile_frags<TW>(J.frags, J.n, TilePos<TW>(J.vw, J.n, J.tiles_x, g - J.tile_base, opaque_tid()), fr);
     for (;;) {
         const int64_t gn = g + G;
         const bool more = gn < tiles;
@@ -918,10 +939,9 @@ __device__ __forceinline__ void persistent_loop(const JobOf &job_of, int64_t til
         float fn[3 * kF];
         auto pf = [&]() {
             if (more)
-                load_tile_frags<TW>(Jn.frags, TilePos<TW>(Jn.vw, Jn.n, Jn.tiles_x, gn - Jn.tile_base, opaque_tid()),
-                                    Jn.vec_ok, fn);
+                load_tile_frags<TW>(Jn.frags, Jn.n, TilePos<TW>(Jn.vw, Jn.n, Jn.tiles_x, gn - Jn.tile_base, opaque_tid()), fn);
         };
-        process_tile_loaded<MODE, TW, WF, WB>(J.m, J.frags, J.vw, J.bias, J.maxd, apron, cap, J.vec_ok, J.out,
+        process_tile_loaded<MODE, TW, WF, WB>(J.m, J.frags, J.vw, J.bias, J.maxd, apron, cap, J.out,
                                               TilePos<TW>(J.vw, J.n, J.tiles_x, g - J.tile_base, opaque_tid()), fr,
                                               sh, s_tex, J.mode == 0, pf);
         if (!more) break;
@@ -938,10 +958,10 @@ __device__ __forceinline__ void persistent_loop(const JobOf &job_of, int64_t til
 template <bool HARD, int TW, class IX>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void tile_kernel(
     MapView m, const float *__restrict__ frags, int64_t n, int64_t vw, int64_t tiles_x, float bias, int maxd,
-    int apron, int cap, int vec_ok, void *__restrict__ out_v, int chunk_log2) {
+    int apron, int cap, void *__restrict__ out_v, int chunk_log2) {
     extern __shared__ float s_tex[];
     __shared__ TileShared sh;
-    process_tile<HARD, TW, kWalkFirst, kWalkSteps, IX>(m, frags, n, vw, tiles_x, bias, maxd, apron, cap, vec_ok, out_v,
+    process_tile<HARD, TW, kWalkFirst, kWalkSteps, IX>(m, frags, n, vw, tiles_x, bias, maxd, apron, cap, out_v,
                                                        xcd_chunked(blockIdx.x, gridDim.x, chunk_log2), sh, s_tex);
 }
 
@@ -972,7 +992,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     const JobDev J = jobs[block_job[g]];
     const int64_t tile = g - J.tile_base;
     process_tile<2, TW, WF, WB, int64_t, true>(J.m, J.frags, J.n, J.vw, J.tiles_x, J.bias, J.maxd, apron, cap,
-                                               J.vec_ok, J.out, tile, sh, s_tex, J.mode == 0);
+                                               J.out, tile, sh, s_tex, J.mode == 0);
 }
 
 // Batched pass with its job records in the kernel arguments: a workgroup
@@ -990,7 +1010,7 @@ struct JobArg {
     int32_t n, vw, tiles_x, tile_base;
     float bias;
     int16_t maxd;
-    uint8_t vec_ok, mode;  // mode 0 hard, 1 RSMSS
+    int16_t mode;          // 0 hard, 1 RSMSS
 };
 
 constexpr int kArgJobsMax = 48;
@@ -1026,7 +1046,7 @@ __device__ __forceinline__ void arg_tile(const BatchArgs &a, int64_t g, int apro
     m.pitch = J.pitch;
     m.W = J.W;
     m.H = J.H;
-    process_tile<2, TW, WF, WB, int, true>(m, J.frags, J.n, J.vw, J.tiles_x, J.bias, J.maxd, apron, cap, J.vec_ok,
+    process_tile<2, TW, WF, WB, int, true>(m, J.frags, J.n, J.vw, J.tiles_x, J.bias, J.maxd, apron, cap,
                                            J.out, g - J.tile_base, sh, s_tex, J.mode == 0);
 }
 
@@ -1087,7 +1107,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(5, 5))) void
 
 // Launch configuration of the main pass (defaults of the plain entry points).
 struct TileConfig {
-    int tile_w;      // 16, 32, 64 (2-D tiles) or 1024 (flat)
+    int tile_w;      // 16, 32 or 64
     int apron;       // texels staged beyond the fragments' texel box, >= 1
     int cap;         // LDS texel capacity per workgroup
     int persistent;  // 0: one workgroup per tile, 1: resident workgroups loop over tiles
@@ -1127,7 +1147,7 @@ inline int64_t resident_groups(const void *kernel, size_t lds) {
 
 template <bool HARD, int TW>
 void launch_tiles(const MapView &mv, const float *frags, int64_t n, int64_t vw, int64_t tiles_x, int64_t tiles,
-                  float bias, int maxd, TileConfig cfg, int vec, void *out, hipStream_t stream) {
+                  float bias, int maxd, TileConfig cfg, void *out, hipStream_t stream) {
     const size_t lds = (size_t)cfg.cap * sizeof(float);
     if (cfg.persistent) {
         JobDev J{};
@@ -1140,7 +1160,6 @@ void launch_tiles(const MapView &mv, const float *frags, int64_t n, int64_t vw, 
         J.tile_base = 0;
         J.bias = bias;
         J.maxd = maxd;
-        J.vec_ok = vec;
         J.mode = HARD ? 0 : 1;
         const void *k = reinterpret_cast<const void *>(&tile_persistent_kernel<HARD, TW>);
         const int64_t grid = std::min<int64_t>(tiles, resident_groups(k, lds));
@@ -1149,32 +1168,52 @@ void launch_tiles(const MapView &mv, const float *frags, int64_t n, int64_t vw, 
     } else {
         if (index32(n, vw, TW))
             hipLaunchKernelGGL((tile_kernel<HARD, TW, int>), dim3((unsigned)tiles), dim3(kT), lds, stream, mv, frags,
-                               n, vw, tiles_x, bias, maxd, cfg.apron, cfg.cap, vec, out, cfg.chunk_log2);
+                               n, vw, tiles_x, bias, maxd, cfg.apron, cfg.cap, out, cfg.chunk_log2);
         else
             hipLaunchKernelGGL((tile_kernel<HARD, TW, int64_t>), dim3((unsigned)tiles), dim3(kT), lds, stream, mv,
-                               frags, n, vw, tiles_x, bias, maxd, cfg.apron, cfg.cap, vec, out, cfg.chunk_log2);
+                               frags, n, vw, tiles_x, bias, maxd, cfg.apron, cfg.cap, out, cfg.chunk_log2);
     }
 }
 
-// Flat launches of few fragments (no screen layout): one lane per fragment,
-// its five texels and its walks read from global memory (L2), the listing's
-// steps per fragment (eval_texel), so every result equals the tile pass's.
-// 1024-fragment tiles would leave most CUs idle (65,536 fragments make 64
-// workgroups), and the texel box of scattered fragments spans the whole map,
-// so staging would not happen anyway.
-constexpr int64_t kFlatFragMax = (int64_t)1 << 20;
+// Flat launches (no screen layout): one lane per fragment, its texels and its
+// walks read from global memory (L2).  The texel box of 1024 consecutive
+// fragments of a list, or of scattered ones, seldom fits LDS, so tiles of them
+// would read global memory all the same, behind a box reduction: 1.6 M
+// fragments of a 1080p view as a list (2048^2 map, RSMSS) 13.6 us here, 24 in
+// tiles; 6.4 M (4K view, 4096^2 map) 46 / 78; 3 M scattered points 125 / 136.
 
 // One fragment's visibility (Listing 1) with the reads of each round issued
-// together: its five texels, then the first two steps of all four walks
-// (24 reads); walks still running continue in blocks of 4 steps.  The same
-// texels and tests as eval_texel, whose walks take one dependent read per
-// step, one walk after the other.  Maps under 4 GiB (32-bit byte offsets).
-template <bool HARD>
+// together: its five texels, then the first two steps of all four walks (24
+// reads); walks still running continue in blocks of 4 steps.  The same texels
+// and tests as the listing, which takes one dependent read per walk step, one
+// walk after the other.  MAP32: a map under 4 GiB (32-bit byte offsets) and at
+// least 3 texels wide (left, centre and right in one 12-byte load: 53 -> 46 us
+// on the 4K list against a test of the width here).
+template <bool HARD, bool MAP32>
 __device__ __forceinline__ float eval_texel_blocked(const MapView &m, const Addr &a, int maxd) {
     const int i0 = a.i0, j0 = a.j0;
     const float zb = a.zb;
-    const float t_c = texel(m, i0, j0), t_l = texel(m, i0 - 1, j0), t_r = texel(m, i0 + 1, j0);
-    const float t_t = texel(m, i0, j0 + 1), t_b = texel(m, i0, j0 - 1);
+    const int ti = clampi(i0, m.W), tj = clampi(j0, m.H), jh = clampi(j0 + 1, m.H), jl = clampi(j0 - 1, m.H);
+    const unsigned pitch4 = 4u * (unsigned)m.pitch;
+    float t_l, t_c, t_r, t_t, t_b;
+    if constexpr (MAP32) {
+        const char *base8 = (const char *)m.t;
+        // the clamped triple starts at column max(ti - 1, 0), at most W - 3
+        const int c3 = min(max(ti - 1, 0), m.W - 3), sc = ti - c3;  // 0 (ti = 0), 1, or 2 (ti = W - 1)
+        const f32x3 t3 = gld3((const float *)(base8 + ((unsigned)tj * pitch4 + 4u * (unsigned)c3)));
+        t_t = gld((const float *)(base8 + ((unsigned)jh * pitch4 + 4u * (unsigned)ti)));
+        t_b = gld((const float *)(base8 + ((unsigned)jl * pitch4 + 4u * (unsigned)ti)));
+        // each clamped by itself: beyond a side of the map all three are the border texel
+        t_c = sc == 0 ? t3.x : (sc == 1 ? t3.y : t3.z);
+        t_l = i0 > m.W - 1 ? t_c : (sc == 2 ? t3.y : t3.x);
+        t_r = i0 < 0 ? t_c : (sc == 0 ? t3.y : t3.z);
+    } else {
+        t_c = texel(m, i0, j0);
+        t_l = texel(m, i0 - 1, j0);
+        t_r = texel(m, i0 + 1, j0);
+        t_t = texel(m, i0, j0 + 1);
+        t_b = texel(m, i0, j0 - 1);
+    }
     const bool s = lit(zb, t_c);
     if (HARD && !s) return 0.0f;
     const unsigned m0 = (lit(zb, t_l) != s ? BIT_L : 0u) | (lit(zb, t_r) != s ? BIT_R : 0u) |
@@ -1182,7 +1221,7 @@ __device__ __forceinline__ float eval_texel_blocked(const MapView &m, const Addr
     if (m0 == 0u) return s ? 1.0f : 0.0f;
     // walks 0 left, 1 right, 2 top, 3 bottom: the moving coordinate p, and the
     // fixed one of the walk's texel and its side neighbours (clamped)
-    GlobalWalkReader rw[4];
+    typename std::conditional<MAP32, GlobalWalkReader, MapLineReader>::type rw[4];
     int p0[4], d[4], pmax[4];
     bool ca[4], cb[4];
 #pragma unroll
@@ -1193,12 +1232,17 @@ __device__ __forceinline__ float eval_texel_blocked(const MapView &m, const Addr
         pmax[dir] = (horiz ? m.W : m.H) - 1;
         ca[dir] = horiz ? (m0 & BIT_T) != 0 : (m0 & BIT_L) != 0;
         cb[dir] = horiz ? (m0 & BIT_B) != 0 : (m0 & BIT_R) != 0;
-        const unsigned fmul = horiz ? 4u * (unsigned)m.pitch : 4u;
-        rw[dir].t = (const char *)m.t;
-        rw[dir].c = (unsigned)(horiz ? clampi(j0, m.H) : clampi(i0, m.W)) * fmul;
-        rw[dir].a = (unsigned)(horiz ? clampi(j0 + 1, m.H) : clampi(i0 - 1, m.W)) * fmul;
-        rw[dir].b = (unsigned)(horiz ? clampi(j0 - 1, m.H) : clampi(i0 + 1, m.W)) * fmul;
-        rw[dir].step4 = horiz ? 4u : 4u * (unsigned)m.pitch;
+        const int fc = horiz ? tj : ti, fa = horiz ? jh : clampi(i0 - 1, m.W), fb = horiz ? jl : clampi(i0 + 1, m.W);
+        if constexpr (MAP32) {
+            const unsigned fmul = horiz ? pitch4 : 4u;
+            rw[dir].t = (const char *)m.t;
+            rw[dir].c = (unsigned)fc * fmul;
+            rw[dir].a = (unsigned)fa * fmul;
+            rw[dir].b = (unsigned)fb * fmul;
+            rw[dir].step4 = horiz ? 4u : pitch4;
+        } else {
+            rw[dir] = MapLineReader{m, fc, fa, fb, horiz};
+        }
     }
     const int first = min(2, maxd);
     float tc[4][2], ta[4][2], tb[4][2];
@@ -1236,43 +1280,40 @@ __device__ __forceinline__ float eval_texel_blocked(const MapView &m, const Addr
     return HARD ? vis_hard(ax, ay) : vis_rsmss(s, ax, ay);
 }
 
-template <bool HARD>
+template <bool HARD, bool MAP32>
 __global__ __launch_bounds__(256) void frag_kernel(MapView m, const float *__restrict__ frags, int64_t n, float bias,
-                                                   int maxd, void *__restrict__ out) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+                                                   int maxd, void *__restrict__ out, int chunk_log2) {
+    const int64_t k = xcd_chunked(blockIdx.x, gridDim.x, chunk_log2) * 256 + threadIdx.x;
     if (k >= n) return;
-    const Addr a = address(gld(frags + 3 * k), gld(frags + 3 * k + 1), gld(frags + 3 * k + 2), m.W, m.H, bias);
-    const bool map_32 = (int64_t)m.pitch * m.H * 4 <= (int64_t)0xFFFFFFFFu;  // byte offsets fit 32 bits
-    const float v = map_32 ? eval_texel_blocked<HARD>(m, a, maxd)
-                           : eval_texel<HARD>(m, a.i0, a.j0, a.fx, a.fy, a.zb, maxd);
+    const f32x3 f = gld3(frags + 3 * k);
+    const Addr a = address(f.x, f.y, f.z, m.W, m.H, bias);
+    const float v = eval_texel_blocked<HARD, MAP32>(m, a, maxd);
     if (HARD) gst(static_cast<uint8_t *>(out) + k, (uint8_t)(v != 0.0f ? 1 : 0));
     else gst(static_cast<float *>(out) + k, v);
 }
 
 template <bool HARD>
-void launch_pass(const MapView &mv, const float *frags, int64_t n, int64_t view_width, float bias, int maxd,
-                 TileConfig cfg, void *out, size_t out_align, hipStream_t stream) {
-    if (view_width <= 0 && n <= kFlatFragMax) {
-        hipLaunchKernelGGL((frag_kernel<HARD>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, mv, frags, n,
-                           bias, maxd, out);
+void launch_pass(const MapView &mv, const float *frags, int64_t n, int64_t vw, float bias, int maxd, TileConfig cfg,
+                 void *out, hipStream_t stream) {
+    if (vw <= 0) {
+        // chunks of 64 workgroups to each XCD: neighbouring fragments of a list
+        // share texels in one L2 (4K list 53 us, single workgroups 55, one
+        // contiguous range each 63)
+        constexpr int kFlatChunkLog2 = 6;
+        const bool map32 = mv.W >= 3 && mv.pitch * mv.H <= (int64_t)(0xFFFFFFFFu / 4u);
+        const auto kernel = map32 ? &frag_kernel<HARD, true> : &frag_kernel<HARD, false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, mv, frags, n, bias, maxd, out,
+                           kFlatChunkLog2);
         return;
     }
-    int64_t vw = view_width;
-    int tw = cfg.tile_w;
-    if (vw <= 0) {  // flat: one row of n pixels, 1024-fragment chunks
-        vw = n;
-        tw = 1024;
-    }
-    const int th = kTileF / tw;
+    const int tw = cfg.tile_w, th = kTileF / tw;
     const int64_t rows = (n + vw - 1) / vw;
     const int64_t tiles_x = (vw + tw - 1) / tw;
     const int64_t tiles = tiles_x * ((rows + th - 1) / th);
-    const int vec = ((uintptr_t)frags % 16 == 0) && ((uintptr_t)out % out_align == 0) && (vw % 4 == 0);
     switch (tw) {
-        case 16: launch_tiles<HARD, 16>(mv, frags, n, vw, tiles_x, tiles, bias, maxd, cfg, vec, out, stream); break;
-        case 64: launch_tiles<HARD, 64>(mv, frags, n, vw, tiles_x, tiles, bias, maxd, cfg, vec, out, stream); break;
-        case 1024: launch_tiles<HARD, 1024>(mv, frags, n, vw, tiles_x, tiles, bias, maxd, cfg, vec, out, stream); break;
-        default: launch_tiles<HARD, 32>(mv, frags, n, vw, tiles_x, tiles, bias, maxd, cfg, vec, out, stream); break;
+        case 16: launch_tiles<HARD, 16>(mv, frags, n, vw, tiles_x, tiles, bias, maxd, cfg, out, stream); break;
+        case 64: launch_tiles<HARD, 64>(mv, frags, n, vw, tiles_x, tiles, bias, maxd, cfg, out, stream); break;
+        default: launch_tiles<HARD, 32>(mv, frags, n, vw, tiles_x, tiles, bias, maxd, cfg, out, stream); break;
     }
 }
 

@@ -1,0 +1,102 @@
+"""Views and lists off every alignment: widths that are no multiple of 4, fewer
+fragments than one thread takes, rows that end in the middle of a thread's
+four, fragment and result pointers off 16 and 4 bytes, fragments beyond every
+side of the map, and maps narrower than the three texels read at once; the
+plain entry points, plans and the engine."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 5
+
+
+@pytest.fixture(scope="module")
+def rb():
+    import paper_1711_07793_amd as rb
+    rb.load_library()
+    return rb
+
+
+def _inputs(W, H, n, vw, seed):
+    rng = np.random.default_rng(seed)
+    m = np.where(rng.random((H, W)) < 0.4, np.float32(0.5), np.float32(0.9)).astype(np.float32)
+    k = np.arange(n)
+    w = vw if vw else 40
+    u = ((k % w) + rng.random(n)) / w * 1.5 - 0.25
+    v = ((k // w) + rng.random(n)) / max(1, (n + w - 1) // w) * 1.5 - 0.25
+    return m, np.stack([u, v, rng.choice([0.45, 0.7, 0.95], n)], 1).astype(np.float32)
+
+
+def _out(n, dtype):
+    """A result tensor that starts off every alignment, and its surroundings."""
+    buf = torch.full((n + 2 * GUARD,), 77, dtype=dtype, device="cuda")
+    return buf[GUARD:GUARD + n], buf
+
+
+@pytest.mark.parametrize("W,H", [(1, 1), (2, 5), (3, 3), (64, 48)])
+@pytest.mark.parametrize("vw", [0, 1, 3, 6, 33, 40])
+def test_views_and_lists_off_alignment(rb, W, H, vw):
+    md = None
+    for n in (1, 2, 3, 4, 5, 7, 130, 255, 1023, 1027, 2051):
+        print(f"lists {W}x{H} vw={vw} n={n}", flush=True)
+        m, f = _inputs(W, H, n, vw, 1000 * W + 10 * n + vw)
+        md = torch.from_numpy(m).cuda()
+        fbuf = torch.empty(3 * n + 1, device="cuda")
+        fbuf[1:] = torch.from_numpy(f.reshape(-1)).cuda()
+        fd = fbuf[1:].view(n, 3)
+        p = dict(width=W, height=H, pitch=W, depth_bias=1e-4, max_dist=9, kernel_radius=0, view_width=vw)
+        want = {0: oracle.rbsm_hard(m, f, p), 1: oracle.rsmss(m, f, p)}
+        jobs, bufs = [], []
+        for mode, dtype, fn in ((0, torch.uint8, rb.rbsm_visibility), (1, torch.float32, rb.rsmss_visibility)):
+            out, buf = _out(n, dtype)
+            fn(md, fd, p, out=out)
+            bufs.append((mode, out, buf))
+            out, buf = _out(n, dtype)
+            jobs.append(dict(map=md, frags=fd, params=p, mode=mode, out=out))
+            bufs.append((mode, out, buf))
+        rb.Plan(jobs).launch()
+        torch.cuda.synchronize()
+        for mode, out, buf in bufs:
+            got = out.cpu().numpy()
+            if mode == 0:
+                assert np.array_equal(got, want[0])
+            else:  # at most two roundings of values up to 1 apart
+                assert np.max(np.abs(got - want[1])) <= 2.0 ** -22
+            around = torch.cat([buf[:GUARD], buf[-GUARD:]])
+            assert bool((around == 77).all())
+
+
+@pytest.mark.parametrize("vw", [0, 6, 33])
+@pytest.mark.parametrize("n", [3, 130, 1027])
+@pytest.mark.parametrize("keep", [False, True])
+def test_engine_composites_off_alignment(rb, n, vw, keep):
+    """One pass for a view's lights and its composite: the composite is the weighted sum of the
+    per-light results, which are stored only when asked for."""
+    W, H = 64, 48
+    m, f = _inputs(W, H, n, vw, 5 * n + vw)
+    fbuf = torch.empty(3 * n + 1, device="cuda")
+    fbuf[1:] = torch.from_numpy(f.reshape(-1)).cuda()
+    fd = fbuf[1:].view(n, 3)
+    p = dict(width=W, height=H, pitch=W, depth_bias=1e-4, max_dist=9, kernel_radius=0, view_width=vw)
+    vis = [oracle.rbsm_hard(m, f, p), oracle.rsmss(m, f, p), oracle.rsmss(m, f, p)]
+    modes, weights = [0, 1, 1], [0.75, 0.3, -1.5]
+    eng = rb.Engine(1 << 20, 4)
+    lid = eng.add_light(torch.from_numpy(m).cuda())
+    comp, cbuf = _out(n, torch.float32)
+    outs = [_out(n, torch.float32 if mode else torch.uint8) for mode in modes]
+    lights = [dict(light=lid, mode=mode, frags=fd, depth_bias=1e-4, max_dist=9, weight=w, out=outs[k][0] if keep else None)
+              for k, (mode, w) in enumerate(zip(modes, weights))]
+    eng.wait(eng.submit(n, lights, view_width=vw, composite=comp))
+    assert np.max(np.abs(comp.cpu().numpy() - oracle.composite(vis, weights))) <= 2.0 ** -20
+    assert bool((torch.cat([cbuf[:GUARD], cbuf[-GUARD:]]) == 77).all())
+    for k, (out, buf) in enumerate(outs):
+        if keep:
+            assert np.max(np.abs(out.cpu().numpy().astype(np.float64) - vis[k])) <= 2.0 ** -22
+            assert bool((torch.cat([buf[:GUARD], buf[-GUARD:]]) == 77).all())
+        else:
+            assert bool((buf == 77).all())
+    eng.close()
