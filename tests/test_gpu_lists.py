@@ -49,7 +49,7 @@ def test_views_and_lists_off_alignment(rb, W, H, vw):
         fbuf[1:] = torch.from_numpy(f.reshape(-1)).cuda()
         fd = fbuf[1:].view(n, 3)
         p = dict(width=W, height=H, pitch=W, depth_bias=1e-4, max_dist=9, kernel_radius=0, view_width=vw)
-        want = {0: oracle.rbsm_hard(m, f, p), 1: oracle.rsmss(m, f, p)}
+        want = {0: oracle.rbsm_hard(m, f, p), 1: oracle.rsmss(m, f, p), 2: oracle.shadow_map(m, f, p)}
         jobs, bufs = [], []
         for mode, dtype, fn in ((0, torch.uint8, rb.rbsm_visibility), (1, torch.float32, rb.rsmss_visibility)):
             out, buf = _out(n, dtype)
@@ -59,15 +59,29 @@ def test_views_and_lists_off_alignment(rb, W, H, vw):
             jobs.append(dict(map=md, frags=fd, params=p, mode=mode, out=out))
             bufs.append((mode, out, buf))
         rb.Plan(jobs).launch()
+        out, buf = _out(n, torch.uint8)
+        rb.sm_visibility(md, fd, p, out=out)
+        bufs.append((2, out, buf))
         torch.cuda.synchronize()
         for mode, out, buf in bufs:
             got = out.cpu().numpy()
-            if mode == 0:
-                assert np.array_equal(got, want[0])
+            if mode != 1:
+                assert np.array_equal(got, want[mode])
             else:  # at most two roundings of values up to 1 apart
                 assert np.max(np.abs(got - want[1])) <= 2.0 ** -22
             around = torch.cat([buf[:GUARD], buf[-GUARD:]])
             assert bool((around == 77).all())
+
+
+@pytest.mark.parametrize("vw,n", [(256, 64 * 256), (256, 64 * 256 - 1), (257, 70 * 257 + 3), (1023, 65 * 1023 - 1), (255, 20000)])
+def test_plain_views_in_tiles(rb, vw, n):
+    """Plain shadow mapping on both sides of the sizes that go in screen tiles, with ragged tiles."""
+    m, f = _inputs(64, 48, n, vw, n)
+    p = dict(width=64, height=48, pitch=64, depth_bias=1e-4, max_dist=9, kernel_radius=0, view_width=vw)
+    out, buf = _out(n, torch.uint8)
+    rb.sm_visibility(torch.from_numpy(m).cuda(), torch.from_numpy(f).cuda(), p, out=out)
+    assert np.array_equal(out.cpu().numpy(), oracle.shadow_map(m, f, p))
+    assert bool((torch.cat([buf[:GUARD], buf[-GUARD:]]) == 77).all())
 
 
 @pytest.mark.parametrize("vw", [0, 6, 33])
