@@ -199,6 +199,10 @@ def _check_inputs(shadow_map: torch.Tensor, frags: torch.Tensor):
 
 def _stream(stream) -> int:
     if stream is None:
+        # the current stream's handle without a Stream object around it (0.2 us a
+        # call instead of 2.9, a third of a small call's time on the host)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
