@@ -45,16 +45,6 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ f32x4u gld4u(const float *p) {
     return *(const __attribute__((address_space(1))) f32x4u *)p;
 }
-// 16-byte store of four floats at 4-byte alignment, 4-byte store at any.
-__device__ __forceinline__ void gst4u(float *p, float x, float y, float z, float w) {
-    f32x4u v;
-    v.x = x; v.y = y; v.z = z; v.w = w;
-    *(__attribute__((address_space(1))) f32x4u *)p = v;
-}
-typedef uint32_t u32u __attribute__((aligned(1)));
-__device__ __forceinline__ void gst_u32(uint8_t *p, uint32_t v) {
-    *(__attribute__((address_space(1))) u32u *)p = v;
-}
 
 // Nearest-texel fetch with clamp-to-edge.
 __device__ __forceinline__ float texel(const MapView &m, int i, int j) {

@@ -213,11 +213,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(7, 7))) void
     const int t = opaque_tid();
     const TilePos<TW, int> P(J.vw, J.n, J.tiles_x, tile, t);
     const lds_float *v = (const lds_float *)s_sum + kF * t;
-    if (P.avail == kF) {
-        gst4u(at(J.out, P.k0), v[0], v[1], v[2], v[3]);
-    } else {
-        for (int f = 0; f < P.avail; ++f) gst(at(J.out, P.k0 + f), v[f]);
-    }
+    for (int f = 0; f < P.avail; ++f) gst(at(J.out, P.k0 + f * P.step), v[f]);
 }
 
 }  // namespace rbsm

@@ -319,66 +319,59 @@ __device__ __forceinline__ T *at(T *p, IX k) {
 }
 
 // Where a thread's 4 pixels of tile `tile_id` sit: a TW x (1024/TW) tile of a
-// row-major image of width vw, each thread 4 consecutive pixels of one row.  Tile and image counts stay below 2^31.
+// row-major image of width vw.  Pixel f of thread t is column t % TW of row
+// t / TW + f * (256 / TW): neighbouring lanes hold neighbouring pixels, so a
+// wave's fragment loads, staged or direct texel reads and result stores each
+// touch one or two runs of memory (with 4 consecutive pixels per thread the
+// lanes are 48 bytes and about 4 texels apart: 8192 x 8192 maps, read
+// directly, took 18.4 us for a 720p hard and 25.7 us for a 1080p RSMSS frame,
+// now 14.7 and 20.4; staged 1080p hard and 4K RSMSS frames, 4096 x 4096 maps:
+// 17.2 -> 16.8 and 36.4 -> 35.5).  Tile and image counts stay below 2^31.
 // IX = int: the caller has checked index32.  IX = int64_t: when every index
 // is below 2^31 (a uniform test) the per-thread arithmetic is still 32-bit.
 template <int TW, class IX = int64_t>
 struct TilePos {
-    IX tyi, txi, px0, k0;
-    int avail;  // how many of the thread's 4 pixels are in the image (0..4)
+    IX tyi, txi, px0, k0, step;  // step: fragments from one pixel of the thread to its next
+    int avail;                   // how many of the thread's 4 pixels, the first ones, are in the image (0..4)
     __device__ __forceinline__ TilePos(int64_t vw, int64_t n, int64_t tiles_x, int64_t tile_id, int t) {
         constexpr int TH = kTileF / TW;
-        constexpr int LPR = TW / kF;
+        constexpr int RS = kT / TW;
         tyi = (IX)((uint32_t)tile_id / (uint32_t)tiles_x);
         txi = (IX)(tile_id - (int64_t)tyi * tiles_x);
+        step = RS * (IX)vw;
         if (sizeof(IX) == 4 || n + (int64_t)TH * vw + TW < ((int64_t)1 << 31)) {
-            const int px = (int)txi * TW + (t % LPR) * kF;
-            const int k = ((int)tyi * TH + t / LPR) * (int)vw + px;
+            const int px = (int)txi * TW + t % TW;
+            const int k = ((int)tyi * TH + t / TW) * (int)vw + px;
             px0 = px;
             k0 = k;
-            avail = max(min(min((int)vw - px, (int)n - k), kF), 0);
+            avail = 0;
+            const bool in = px < (int)vw;
+#pragma unroll
+            for (int f = 0; f < kF; ++f) avail += (int)(in & (k + f * (int)step < (int)n));
         } else {
-            px0 = (IX)((int64_t)txi * TW + (int64_t)(t % LPR) * kF);
-            k0 = (IX)(((int64_t)tyi * TH + t / LPR) * vw + px0);
-            const int64_t lim = min(vw - (int64_t)px0, n - (int64_t)k0);
-            avail = (int)max(min(lim, (int64_t)kF), (int64_t)0);
+            px0 = (IX)((int64_t)txi * TW + t % TW);
+            k0 = (IX)(((int64_t)tyi * TH + t / TW) * vw + px0);
+            avail = 0;
+            const bool in = px0 < (IX)vw;
+#pragma unroll
+            for (int f = 0; f < kF; ++f) avail += (int)(in & (k0 + f * step < (IX)n));
         }
     }
 };
 
-// Fragment loads of one thread for one tile: one 48-byte load (three 16-byte
-// ones, dword aligned: rows and lists of any length start anywhere).  A
-// thread whose pixels run past a row's end reads the next row's with it; past
-// the last fragment it reads the last four, shifted into place.  Values of
-// pixels outside the image are never used.  Fewer than four fragments are read
-// one by one.
+// Fragment loads of one thread for one tile: a 12-byte load per fragment
+// (dword aligned: rows and lists of any length start anywhere).  A pixel past
+// its row's end reads the next row's fragment, one past the last fragment
+// reads the last; their values are never used.
 template <int TW, class IX>
 __device__ __forceinline__ void load_tile_frags(const float *__restrict__ frags, int64_t n, const TilePos<TW, IX> &P,
                                                 float (&fr)[3 * kF]) {
-    const IX last = (IX)n - kF;
-    const IX k = P.k0 < last ? P.k0 : last;
-    if (last >= 0) {
-        const float *p = at(frags, 3 * k);
-        const f32x4u a = gld4u(p), b = gld4u(p + 4), c = gld4u(p + 8);
-        fr[0] = a.x; fr[1] = a.y; fr[2] = a.z; fr[3] = a.w;
-        fr[4] = b.x; fr[5] = b.y; fr[6] = b.z; fr[7] = b.w;
-        fr[8] = c.x; fr[9] = c.y; fr[10] = c.z; fr[11] = c.w;
-        if (P.k0 > k) {
+    const IX last = (IX)n - 1;
 #pragma unroll
-            for (int s = 0; s < kF - 1; ++s)
-                if (P.k0 - k > s) {
-#pragma unroll
-                    for (int q = 0; q < 3 * (kF - 1); ++q) fr[q] = fr[q + 3];
-                }
-        }
-    } else {
-#pragma unroll
-        for (int f = 0; f < kF; ++f) {
-            const IX k3 = f < P.avail ? 3 * (P.k0 + f) : 0;
-            fr[3 * f + 0] = gld(at(frags, k3));
-            fr[3 * f + 1] = gld(at(frags, k3 + 1));
-            fr[3 * f + 2] = gld(at(frags, k3 + 2));
-        }
+    for (int f = 0; f < kF; ++f) {
+        const IX k = P.k0 + f * P.step;
+        const f32x3 a = gld3(at(frags, 3 * (k < last ? k : last)));
+        fr[3 * f] = a.x; fr[3 * f + 1] = a.y; fr[3 * f + 2] = a.z;
     }
 }
 
@@ -433,7 +426,7 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
                                                     const TileSum &sum = TileSum{}) {
     const bool HARD = MODE == 2 ? hard_rt : MODE == 1;
     constexpr int TH = kTileF / TW;
-    constexpr int LPR = TW / kF;
+    constexpr int RS = kT / TW;
     auto &s_box = sh.box;
     auto &q_slot = sh.slot;
     auto &q_sm = sh.sm;
@@ -445,7 +438,7 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
 
     const int t = opaque_tid();
     const int lane = t & 63, wave = t >> 6;
-    const IX tyi = P.tyi, txi = P.txi, k0 = P.k0, vw = (IX)vw64;
+    const IX tyi = P.tyi, txi = P.txi, vw = (IX)vw64;
     const unsigned long long below = (1ull << lane) - 1ull;  // lanes below this one (from the opaque index)
 
     Staged st;
@@ -453,7 +446,6 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
         bool valid[kF];
 #pragma unroll
         for (int f = 0; f < kF; ++f) valid[f] = f < P.avail;
-        const bool full = valid[kF - 1];
 
         // cap == 0: direct reads, no box and no staging.  The queue counters
         // are cleared before the first fragment value is used, so the
@@ -620,38 +612,11 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
         }
 
         // final results of every fragment that is not an edge fragment
-        const bool any_edge = edge[0] | edge[1] | edge[2] | edge[3];
         if constexpr (SUM) {
 #pragma unroll
             for (int f = 0; f < kF; ++f)
                 if (!edge[f]) sum.add(kF * t + f, s[f] ? 1.0f : 0.0f);
         }
-        if (SUM && out_v == nullptr) {
-            // the sums alone
-        } else if (HARD) {
-            uint8_t *out = static_cast<uint8_t *>(out_v);
-            if (full && !any_edge) {
-                uint32_t packed = 0;
-#pragma unroll
-                for (int f = 0; f < kF; ++f) packed |= (uint32_t)(s[f] ? 1u : 0u) << (8 * f);
-                gst_u32(at(out, k0), packed);
-            } else {
-#pragma unroll
-                for (int f = 0; f < kF; ++f)
-                    if (valid[f] && !edge[f]) gst(at(out, k0 + f), (uint8_t)(s[f] ? 1 : 0));
-            }
-        } else {
-            float *out = static_cast<float *>(out_v);
-            if (full && !any_edge) {
-                gst4u(at(out, k0), s[0] ? 1.0f : 0.0f, s[1] ? 1.0f : 0.0f, s[2] ? 1.0f : 0.0f, s[3] ? 1.0f : 0.0f);
-            } else {
-#pragma unroll
-                for (int f = 0; f < kF; ++f)
-                    if (valid[f] && !edge[f]) gst(at(out, k0 + f), s[f] ? 1.0f : 0.0f);
-            }
-        }
-
-        // queue the edge fragments: wave ballots, one LDS atomic per wave
         unsigned long long bal[kF];
         int wave_total = 0;
 #pragma unroll
@@ -659,6 +624,26 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
             bal[f] = __ballot(edge[f]);
             wave_total += __popcll(bal[f]);
         }
+        // where the thread's results go, from a fresh copy of its index: held
+        // since the fragment loads, it is the registers that spill (at 64 per
+        // wave, 8 waves per SIMD; a 4K hard frame took 39.6 us for 29.6)
+        const int t_out = opaque_tid();
+        const IX k_out = (tyi * TH + t_out / TW) * vw + (txi * TW + (IX)(t_out % TW)), step = RS * vw;
+        if (SUM && out_v == nullptr) {
+            // the sums alone
+        } else if (HARD) {
+            uint8_t *out = static_cast<uint8_t *>(out_v);
+#pragma unroll
+            for (int f = 0; f < kF; ++f)
+                if (valid[f] && !edge[f]) gst(at(out, k_out + f * step), (uint8_t)(s[f] ? 1 : 0));
+        } else {
+            float *out = static_cast<float *>(out_v);
+#pragma unroll
+            for (int f = 0; f < kF; ++f)
+                if (valid[f] && !edge[f]) gst(at(out, k_out + f * step), s[f] ? 1.0f : 0.0f);
+        }
+
+        // queue the edge fragments: wave ballots, one LDS atomic per wave
         if (wave_total) {
             int base = 0;
             if (lane == 0) base = atomicAdd(&q_count, wave_total);
@@ -687,7 +672,7 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
     auto frag_of = [&](int e) -> IX {
         const int slot = q_slot[e];
         const int owner = slot >> 2, f = slot & 3;
-        return (tyi * TH + owner / LPR) * vw + txi * TW + (IX)(owner % LPR) * kF + f;
+        return (tyi * TH + owner / TW + f * RS) * vw + txi * TW + (IX)(owner % TW);
     };
     // texel and biased depth of queue entry e (from LDS, or recomputed past
     // kState); the sub-texel position, needed only by the last step, is

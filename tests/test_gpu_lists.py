@@ -114,3 +114,40 @@ def test_engine_composites_off_alignment(rb, n, vw, keep):
         else:
             assert bool((buf == 77).all())
     eng.close()
+
+
+@pytest.mark.parametrize("tile_w", [16, 32, 64])
+@pytest.mark.parametrize("vw,n", [(1, 70), (15, 15 * 65 + 1), (31, 31 * 33 - 1), (64, 64 * 16), (65, 65 * 31 + 64), (130, 130 * 66 + 7)])
+def test_tile_edges(rb, tile_w, vw, n):
+    """Views that end inside a tile on either side and in the middle of a row, at every tile width, hard and soft."""
+    m, f = _inputs(64, 48, n, vw, n)
+    p = dict(width=64, height=48, pitch=64, depth_bias=1e-4, max_dist=9, kernel_radius=0, view_width=vw)
+    md, fd = torch.from_numpy(m).cuda(), torch.from_numpy(f).cuda()
+    for hard, dtype, fn in ((True, torch.uint8, oracle.rbsm_hard), (False, torch.float32, oracle.rsmss)):
+        want = fn(m, f, p)
+        for persistent in (0, 1):
+            out, buf = _out(n, dtype)
+            rb.rbsm_pass_tuned(0 if hard else 1, md, fd, p, (tile_w, 1, 2048, persistent, 0, 0, 3), out=out)
+            got = out.cpu().numpy()
+            if hard:
+                assert np.array_equal(got, want)
+            else:  # at most two roundings of values up to 1 apart
+                assert np.max(np.abs(got - want)) <= 2.0 ** -22
+            assert bool((torch.cat([buf[:GUARD], buf[-GUARD:]]) == 77).all())
+
+
+@pytest.mark.parametrize("n", [2 ** 28 + 5, 2 ** 31 - 1])
+def test_views_past_32_bit_indices(rb, n):
+    """A view whose fragment indices need the 64-bit forms: the bits of the same fragments given as a list."""
+    m, _ = _inputs(64, 48, 4, 0, 5)
+    md = torch.from_numpy(m).cuda()
+    f = torch.empty((n, 3), device="cuda").uniform_(-0.02, 1.02, generator=torch.Generator(device="cuda").manual_seed(3))
+    p = dict(width=64, height=48, pitch=64, depth_bias=1e-4, max_dist=9, kernel_radius=0, view_width=0)
+    want = rb.rbsm_visibility(md, f, p)
+    print(f"views n={n}", flush=True)
+    view = dict(p, view_width=4099)
+    assert torch.equal(rb.rbsm_visibility(md, f, view), want)
+    got = torch.full_like(want, 77)
+    plan = rb.Plan([dict(map=md, frags=f, params=view, mode=0, out=got)])
+    plan.launch()
+    assert torch.equal(got, want)
