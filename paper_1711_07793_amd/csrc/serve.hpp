@@ -43,8 +43,16 @@ constexpr int kServeMaxReqs = 64;    // requests per scheduling step
 constexpr int kServeSlots = 2;       // steps whose compute may be pending
 constexpr int kArgJobs = 40;         // tile jobs per launch, passed in the kernel arguments
 constexpr int kArgComp = 20;         // composites per launch, passed in the kernel arguments
-constexpr int kServeTileW = 64;      // tile width of the merged jobs (as in the batched autotuner's choice)
-constexpr int kServeChunkLog2 = 5;   // merged jobs' tiles dealt to XCDs in chunks of 32 (balances XCDs)
+// Tiles of the merged jobs and how many consecutive ones go to one XCD.  32 x
+// 32 tiles have the smaller texel boxes on magnified and minified maps alike
+// (more of them are staged, and those hold fewer texels), and jobs of very
+// different cost balance better in small chunks: a step of 32 requests, 84
+// (view, light) passes over maps of 1024..8192, takes 1597 us at 64 and 32
+// tiles, 1585 at 64 and 8, 1525 at 32 and 16, 1518 at 32 and 8, 1555 at 32 and 4
+// (where 32 and 8 takes 1539); without composites 1572 and 1525 us at the first
+// and the last choice.
+constexpr int kServeTileW = 32;
+constexpr int kServeChunkLog2 = 3;
 
 // One view's composite: out[k] = sum_l w[l] * vis_l[k].
 struct CompJob {
