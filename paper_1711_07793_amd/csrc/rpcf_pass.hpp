@@ -134,8 +134,12 @@ __device__ __forceinline__ float win_axis(WalkEnd n, WalkEnd p, float f, const l
 // 0.46 / 0.63, 1080p r = 13 2.23 / 1.75 -> 1.09 / 0.99, 720p r = 15 2.11 / 3.31
 // -> 0.88 / 0.88, 640x360 r = 32 (one lane per fragment before) 26.5 -> 1.4.
 // Keeping both kinds of words at 16 bits up to NR = 16 gives 28 waves per CU.
+// Waves per SIMD: what LDS leaves room for.  MULTI at NR = 24 fits 6 workgroups
+// (3 waves per SIMD, 163 VGPRs): held to 4 waves it spilled 24 registers, and
+// 762 MB of a 4K r = 15 frame's writes were scratch (720p r = 21 1174 us, now
+// 1109; r = 32 2084, now 1965).
 template <int NR, bool MULTI>
-__global__ __launch_bounds__(kRpcfT) __attribute__((amdgpu_waves_per_eu(NR <= 16 ? 7 : 4))) void
+__global__ __launch_bounds__(kRpcfT) __attribute__((amdgpu_waves_per_eu(NR <= 16 ? 7 : MULTI && NR == 24 ? 3 : 4))) void
 rpcf_window_kernel(
     MapView m, const float *__restrict__ frags, int64_t n, int64_t vw, int64_t tiles_x, int tw_log2, float bias,
     int maxd, int r, int parts, int part_side, int cap, int list_cap, int chunk_log2, float *__restrict__ out) {
@@ -514,11 +518,17 @@ void launch_window(const MapView &mv, const float *frags, int64_t n, int64_t vie
 // to r = 6: fewer tests, but more traversals leave it).  Beyond r = 14 the box
 // goes in parts of at most 22 x 22 terms, whose 24 x 24 windows leave LDS for
 // 6 workgroups per CU; parts of 30 terms (32 x 32 windows) leave it for 4.
+// Parts of at most 18 terms a side (r = 15..17 in two, 22..26 in three) take 20
+// x 20 windows, which test 30% fewer texels and leave LDS for 8 workgroups: 720p r =
+// 15 787 -> 709 us, r = 22 1421 -> 1178 (24 x 24 at 4 waves per SIMD before).
 inline void launch_rpcf(const MapView &mv, const float *frags, int64_t n, int64_t view_width, float bias, int maxd,
                         int r, float *out, hipStream_t stream) {
     if (r > kWinMaxR) {
         const int parts = (2 * r + kWinPart) / kWinPart;  // of 2r+1 terms
-        launch_window<24, true>(mv, frags, n, view_width, bias, maxd, r, parts, out, stream);
+        if ((2 * r + parts) / parts <= 18)
+            launch_window<20, true>(mv, frags, n, view_width, bias, maxd, r, parts, out, stream);
+        else
+            launch_window<24, true>(mv, frags, n, view_width, bias, maxd, r, parts, out, stream);
         return;
     }
     switch ((2 * r + 3 + 3) & ~3) {

@@ -47,7 +47,7 @@ def _view(W, H, vw, vh, step, x0, y0, rng):
 
 @pytest.mark.parametrize("r,max_dist", [(1, 1), (2, 64), (3, 5), (4, 31), (5, 32), (6, 16), (7, 33), (8, 64), (9, 2),
                                         (10, 16), (11, 40), (12, 16), (13, 64), (14, 16), (14, 64), (15, 16),
-                                        (16, 64), (21, 8), (22, 64), (32, 64)])
+                                        (16, 64), (17, 16), (18, 64), (21, 8), (22, 64), (26, 8), (27, 64), (32, 64)])
 def test_every_window(rb, r, max_dist):
     rng = np.random.default_rng(100 * r + max_dist)
     W, H = 331, 243
