@@ -287,9 +287,8 @@ typedef struct {
  *   n_prims     >= 0
  *   r0, ru, rv  receiver plane
  *   shadow_map  [height*pitch] float32 device output, row-major (columns >=
- *               width untouched); must not overlap prims.  Any alignment is
- *               accepted; a 16-byte-aligned map with pitch a multiple of 4
- *               is written with 16-byte stores (faster)
+ *               width untouched); must not overlap prims.  Any alignment and
+ *               pitch run at the same rate
  */
 int rbsm_rasterize(const rbsm_prim *prims, int32_t n_prims, double r0, double ru, double rv, int32_t width,
                    int32_t height, int64_t pitch, float *shadow_map, hipStream_t stream);
@@ -333,9 +332,10 @@ int rbsm_composite(int64_t n, int32_t n_lights, const void *const *vis, const in
  * working sets of all admitted requests -- every light's fragments (12 B per
  * fragment) and result (1 or 4 B), and the composite (4 B), wherever they
  * live -- stay within hbm_budget_bytes.  Each scheduling step runs one
- * batched pass over the jobs of every admitted request (each per-light result
- * is bitwise the plain entry point's), the RPCF jobs, and one compositing
- * launch.  Requests that arrive while others run join the next step.
+ * batched pass over the views of every admitted request that wants a composite
+ * (composite included) and one over the jobs of the others (each per-light
+ * result is bitwise the plain entry point's); requests with an RPCF light take
+ * an RPCF pass per such light and a compositing launch.  Requests that arrive while others run join the next step.
  * Results are the same alone and in any mix.
  *
  * Stream order: a request's kernels wait for everything enqueued on its

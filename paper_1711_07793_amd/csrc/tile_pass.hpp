@@ -49,7 +49,7 @@ __device__ __forceinline__ int64_t xcd_chunked(int b, int nb, int chunk_log2) {
 // ---------------------------------------------------------------------------
 
 constexpr int kT = 256;            // threads per workgroup
-constexpr int kF = 4;              // consecutive pixels per thread
+constexpr int kF = 4;              // pixels per thread
 constexpr int kTileF = kT * kF;    // fragments per tile
 constexpr int kState = 128;        // edge fragments whose full state is kept in LDS
 constexpr int kWalkFirst = 2;     // default: steps every walk takes before the unfinished ones are compacted
