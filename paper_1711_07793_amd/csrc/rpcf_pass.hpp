@@ -119,7 +119,9 @@ __device__ __forceinline__ float win_axis(WalkEnd n, WalkEnd p, float f, const l
 //
 // Results are summed as integers: a term v in [0, 1] adds the bits of 1 + v
 // (binary64), a multiple of 2^-52, so the sum does not depend on the order of
-// the list, and each term is rounded by at most 2^-53.
+// the list, and each term is rounded by at most 2^-53.  64 bits hold fewer than
+// 4096 such terms of value 1: a box in one part has at most 29^2, and after each
+// of several parts the whole part of the sum moves to a counter of its own.
 //
 // A wave whose fragments all pass, or all fail, every test of the band (the
 // band's depth range against theirs) is done at once: the mean is 1 or 0.
@@ -210,6 +212,10 @@ rpcf_window_kernel(
         return xrows + lane + (q < 0 ? y : y - N) * 64;  // rows 0 .. k0 - 1, then k0 + N .. NR - 1
     };
     int lit_terms = 0, edge_terms = 0;  // of this lane
+    // this lane's listed terms, in units of 2^-52
+    auto edge_sum = [&]() -> unsigned long long {
+        return s_sum[t] - (unsigned long long)edge_terms * 0x3ff0000000000000ull;
+    };
     // One part of the box.  True where every lane's tests are all the same
     // (plain_lit: lit), which its terms then are.
     auto run_part = [&](int part, bool &plain_lit) -> bool {
@@ -471,6 +477,16 @@ rpcf_window_kernel(
             if (lane < left) list[lane] = keep;
             listed = left;
         }
+        if (MULTI) {
+            // the whole part of the sum joins the lit terms: up to 65^2 terms of
+            // value 1 do not fit 64 bits at 2^-52, those of one part (at most
+            // kWinPart^2) and a remainder below 1 do
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const unsigned long long sum = edge_sum();
+            lit_terms += (int)(sum >> 52);
+            s_sum[t] = sum & ((1ull << 52) - 1ull);
+            edge_terms = 0;
+        }
         return false;
     };
     bool plain_lit = false;
@@ -482,8 +498,7 @@ rpcf_window_kernel(
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (valid) {
-        const unsigned long long sum = s_sum[t] - (unsigned long long)edge_terms * 0x3ff0000000000000ull;
-        const double acc = (double)lit_terms + (double)sum * 0x1p-52;
+        const double acc = (double)lit_terms + (double)edge_sum() * 0x1p-52;
         out[k] = (float)(acc / (double)((2 * r + 1) * (2 * r + 1)));
     }
 }
