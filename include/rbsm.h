@@ -91,10 +91,11 @@ int rbsm_visibility(const float *shadow_map, const float *frags, int64_t n, cons
  * (2r+1)^2 texels (i0+a, j0+b), |a|, |b| <= r, with the fragment's own
  * sub-texel position and depth, averaged (PCF over the filtered edge,
  * Sec. 5.3): the exact mean of those binary32 values rounded to binary32.
- * It is computed as a binary64 sum in an unspecified order divided once by
- * (2r+1)^2, which stays within 5e-13 of the exact mean, so the result is the
- * rounded exact mean except at a near-tie, where it may be the neighbouring
- * binary32 value.
+ * Values of 2^-29 and more are summed exactly, smaller ones in binary64 in an
+ * unspecified order, and the sum is divided once by (2r+1)^2 in binary64.
+ * That stays within 5e-13 of the exact mean, and within 2^-40 of it
+ * relatively, so the result is the rounded exact mean except at a near-tie,
+ * where it may be the neighbouring binary32 value.
  *   out_vis     [n] float32 written: visibility in [0, 1], fragment order
  * Other arguments as rbsm_visibility.
  */

@@ -17,10 +17,11 @@
 // parts, one after the other.
 //
 // The average is the exact mean of the (2r+1)^2 binary32 terms, rounded to
-// binary32.  Terms are summed as integers (multiples of 2^-52) and the sum is
-// divided by (2r+1)^2 once, in binary64: it stays within 5e-13 of the exact
-// mean, so the result is that mean rounded, up to one binary32 step at a
-// near-tie, and does not depend on the order of the terms.
+// binary32.  Terms are summed as integers (multiples of 2^-52), what that
+// leaves of the rare terms below 2^-29 in binary64, and the sum is divided by
+// (2r+1)^2 once, in binary64: it stays within 5e-13 of the exact mean and
+// within 2^-40 of it relatively, so the result is that mean rounded, up to one
+// binary32 step at a near-tie.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -38,6 +39,7 @@ constexpr int kRpcfT = 128;      // threads per workgroup, one fragment each
 constexpr int kWinMaxR = 14;     // largest r whose 2r+3 rows and columns fit 32-bit words
 constexpr int kWinPart = 22;     // beyond it: terms per side of a part, at most
 constexpr int kWinLate = 128;    // terms per wave with a traversal that leaves the window
+constexpr float kWinSmall = 0x1p-29f;  // a binary32 value from here on is a multiple of 2^-52
 
 // Shadow-test bit of texel depth t for depth zb (Eq. 1): the sign bit of
 // t - zb.  The difference is negative exactly when zb > t, except for
@@ -119,7 +121,11 @@ __device__ __forceinline__ float win_axis(WalkEnd n, WalkEnd p, float f, const l
 //
 // Results are summed as integers: a term v in [0, 1] adds the bits of 1 + v
 // (binary64), a multiple of 2^-52, so the sum does not depend on the order of
-// the list, and each term is rounded by at most 2^-53.  64 bits hold fewer than
+// the list.  Only a term below 2^-29 can have bits under 2^-52: a ballot finds
+// those, and their rounding errors are added to the fragment's own binary64
+// sum one at a time.  (Looking for them costs 2% up to r = 6 and beyond r = 14,
+// where the two registers of that sum are dear, nothing between; a second
+// listing of their waves' terms cost 2-6%.)  64 bits hold fewer than
 // 4096 such terms of value 1: a box in one part has at most 29^2, and after each
 // of several parts the whole part of the sum moves to a counter of its own.
 //
@@ -212,6 +218,7 @@ rpcf_window_kernel(
         return xrows + lane + (q < 0 ? y : y - N) * 64;  // rows 0 .. k0 - 1, then k0 + N .. NR - 1
     };
     int lit_terms = 0, edge_terms = 0;  // of this lane
+    double rest = 0.0;                  // of its listed terms, what s_sum leaves out
     // this lane's listed terms, in units of 2^-52
     auto edge_sum = [&]() -> unsigned long long {
         return s_sum[t] - (unsigned long long)edge_terms * 0x3ff0000000000000ull;
@@ -409,7 +416,17 @@ rpcf_window_kernel(
     };
         auto add = [&](uint32_t en, float v) {
             atomicAdd(&s_sum[wave * 64 + (en & 63u)], (unsigned long long)__double_as_longlong(1.0 + (double)v));
-    };
+        };
+        // a small term, not 0: s_sum rounds it
+        auto is_small = [&](float v) { return __float_as_uint(v) - 1u < __float_as_uint(kWinSmall) - 1u; };
+        // what was rounded off goes to the fragments' lanes, one term (a bit of `which`) at a time
+        auto add_small = [&](uint32_t en, float v, unsigned long long which) {
+            for (; which != 0ull; which &= which - 1ull) {
+                const int from = __builtin_ctzll(which);
+                const double x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from));
+                if (lane == (__builtin_amdgcn_readlane((int)en, from) & 63)) rest += x - ((1.0 + x) - 1.0);
+            }
+        };
 
         const uint32_t range = valid ? ((2u << (nx - 1)) - 1u) << c0 : 0u;  // the part's columns
         const int y1 = c0 + ny - 1;
@@ -455,9 +472,14 @@ rpcf_window_kernel(
                 const float v = term(en, std::false_type{}, leaves);
                 leaves = leaves && on;
                 if (on && !leaves) add(en, v);
-                const unsigned long long lv = __ballot(leaves);
-                if (leaves) late[n_late + below(lv)] = (uint16_t)en;
-                n_late += __builtin_popcountll(lv);
+                // (the ballots of bools stay scalar masks; __ballot goes through an int)
+                const unsigned long long lv = __builtin_amdgcn_ballot_w64(leaves);
+                const unsigned long long sm = __builtin_amdgcn_ballot_w64(is_small(v));
+                if ((lv | sm) != 0ull) {
+                    if (leaves) late[n_late + below(lv)] = (uint16_t)en;
+                    n_late += __builtin_popcountll(lv);
+                    add_small(en, v, sm & ~lv & __builtin_amdgcn_ballot_w64(on));
+                }
                 // the terms that left the window, a full wave of them at a time
                 while (n_late >= 64 || (last && e + 64 >= todo && n_late > 0)) {
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -468,6 +490,7 @@ rpcf_window_kernel(
                     bool unused;
                     const float lval = term(el, std::true_type{}, unused);
                     if (lon) add(el, lval);
+                    add_small(el, lval, __ballot(lon && is_small(lval)));
                     n_late = from;
                 }
             }
@@ -498,7 +521,7 @@ rpcf_window_kernel(
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (valid) {
-        const double acc = (double)lit_terms + (double)edge_sum() * 0x1p-52;
+        const double acc = (double)lit_terms + ((double)edge_sum() * 0x1p-52 + rest);
         out[k] = (float)(acc / (double)((2 * r + 1) * (2 * r + 1)));
     }
 }
