@@ -574,11 +574,11 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
                     // texel is the clamp)
                     const unsigned c3 = (unsigned)min(max(ti[f] - 1, 0), m.W - 3);
                     sc[f] = ti[f] - (int)c3;  // 0 (ti = 0), 1, or 2 (ti = W-1)
-                    t3[f] = gld3((const float *)(base8 + (__umul24((unsigned)tj[f], pitch4) + 4u * c3)));
+                    t3[f] = gld3((const float *)(base8 + ((unsigned)tj[f] * pitch4 + 4u * c3)));
                     const int jl = max(tj[f] - 1, 0), jh = min(tj[f] + 1, m.H - 1);
-                    // 24-bit multiplies: rows below 2^16, pitch4 below 2^18
-                    tc[f][3] = gld((const float *)(base8 + (__umul24((unsigned)jh, pitch4) + 4u * (unsigned)ti[f])));
-                    tc[f][4] = gld((const float *)(base8 + (__umul24((unsigned)jl, pitch4) + 4u * (unsigned)ti[f])));
+                    // full multiplies: a map of few rows may have a pitch of any size
+                    tc[f][3] = gld((const float *)(base8 + ((unsigned)jh * pitch4 + 4u * (unsigned)ti[f])));
+                    tc[f][4] = gld((const float *)(base8 + ((unsigned)jl * pitch4 + 4u * (unsigned)ti[f])));
                 }
 #pragma unroll
                 for (int f = 0; f < kF; ++f) {

@@ -151,3 +151,33 @@ def test_views_past_32_bit_indices(rb, n):
     plan = rb.Plan([dict(map=md, frags=f, params=view, mode=0, out=got)])
     plan.launch()
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("pitch,H", [(2 ** 22 - 1, 200), (2 ** 22, 200), (5_000_001, 100), (2 ** 30 - 64, 1), (2 ** 29, 2)])
+def test_long_pitch(rb, pitch, H):
+    """Narrow maps whose rows lie far apart, below and above the 2^24 bytes a row that 24-bit
+    multiplies could take, with fragments spread over them so that their texels do not fit LDS: views, plans and the engine."""
+    W, vw, n = 64, 33, 33 * 70
+    m, f = _inputs(W, H, n, vw, 11)
+    f = f[np.random.default_rng(1).permutation(n)]  # every tile spans the map
+    full = torch.full((H, pitch), float("nan"), device="cuda")  # reads beside the map differ from it
+    md = full[:, :W]
+    md.copy_(torch.from_numpy(m))
+    fd = torch.from_numpy(f).cuda()
+    eng = rb.Engine(1 << 20, 4)
+    lid = eng.add_light(md)
+    for view_width in (vw, 0):
+        p = dict(width=W, height=H, pitch=pitch, depth_bias=1e-4, max_dist=9, kernel_radius=0, view_width=view_width)
+        want = {0: oracle.rbsm_hard(m, f, dict(p, pitch=W)), 1: oracle.rsmss(m, f, dict(p, pitch=W))}
+        for mode, dtype, fn in ((0, torch.uint8, rb.rbsm_visibility), (1, torch.float32, rb.rsmss_visibility)):
+            print(f"pitch {pitch} vw={view_width} mode={mode}", flush=True)
+            got = [fn(md, fd, p), rb.rbsm_pass_tuned(mode, md, fd, p, (32, 1, 0, 0, 0, 0, 3)),
+                   rb.rbsm_pass_tuned(mode, md, fd, p, (16, 1, 256, 1, 0, 0, 3))]
+            got += [torch.empty(n, dtype=dtype, device="cuda") for _ in range(2)]
+            rb.Plan([dict(map=md, frags=fd, params=p, mode=mode, out=got[3])]).launch()
+            eng.wait(eng.submit(n, [dict(light=lid, mode=mode, frags=fd, depth_bias=1e-4, max_dist=9, out=got[4])],
+                                view_width=view_width))
+            torch.cuda.synchronize()
+            for g in got:  # at most two roundings of values up to 1 apart
+                assert np.max(np.abs(g.cpu().numpy().astype(np.float64) - want[mode])) <= (0 if mode == 0 else 2.0 ** -22)
+    eng.close()
