@@ -626,21 +626,24 @@ __device__ __forceinline__ void process_tile_loaded(MapView m, const float *__re
         }
         // where the thread's results go, from a fresh copy of its index: held
         // since the fragment loads, it is the registers that spill (at 64 per
-        // wave, 8 waves per SIMD; a 4K hard frame took 39.6 us for 29.6)
+        // wave, 8 waves per SIMD; a 4K hard frame took 39.6 us for 29.6).  A
+        // result's index is below 2^31: unsigned 32-bit arithmetic holds it in
+        // the 64-bit form too, where 64-bit indices spilled 6 registers
         const int t_out = opaque_tid();
-        const IX k_out = (tyi * TH + t_out / TW) * vw + (txi * TW + (IX)(t_out % TW)), step = RS * vw;
+        const uint32_t step = RS * (uint32_t)vw;
+        const uint32_t k_out = (uint32_t)(tyi * TH + t_out / TW) * (uint32_t)vw + (uint32_t)(txi * TW + t_out % TW);
         if (SUM && out_v == nullptr) {
             // the sums alone
         } else if (HARD) {
             uint8_t *out = static_cast<uint8_t *>(out_v);
 #pragma unroll
             for (int f = 0; f < kF; ++f)
-                if (valid[f] && !edge[f]) gst(at(out, k_out + f * step), (uint8_t)(s[f] ? 1 : 0));
+                if (valid[f] && !edge[f]) gst(at(out, (IX)(k_out + f * step)), (uint8_t)(s[f] ? 1 : 0));
         } else {
             float *out = static_cast<float *>(out_v);
 #pragma unroll
             for (int f = 0; f < kF; ++f)
-                if (valid[f] && !edge[f]) gst(at(out, k_out + f * step), s[f] ? 1.0f : 0.0f);
+                if (valid[f] && !edge[f]) gst(at(out, (IX)(k_out + f * step)), s[f] ? 1.0f : 0.0f);
         }
 
         // queue the edge fragments: wave ballots, one LDS atomic per wave
