@@ -333,10 +333,12 @@ int rbsm_composite(int64_t n, int32_t n_lights, const void *const *vis, const in
  * working sets of all admitted requests -- every light's fragments (12 B per
  * fragment) and result (1 or 4 B), and the composite (4 B), wherever they
  * live -- stay within hbm_budget_bytes.  Each scheduling step runs one
- * batched pass over the views of every admitted request that wants a composite
- * (composite included) and one over the jobs of the others (each per-light
- * result is bitwise the plain entry point's); requests with an RPCF light take
- * an RPCF pass per such light and a compositing launch.  Requests that arrive while others run join the next step.
+ * batched pass over the jobs of every admitted request (each per-light result
+ * is bitwise the plain entry point's), an RPCF pass per RPCF light, and one
+ * compositing launch; composites of views that fill the GPU, and of single
+ * lights, are formed in a pass of their own, without a per-light result that
+ * the caller did not ask for.  Requests that arrive while others run join the
+ * next step.
  * Results are the same alone and in any mix.
  *
  * Stream order: a request's kernels wait for everything enqueued on its

@@ -189,6 +189,14 @@ struct ViewJob {
 };
 
 constexpr int kViewCap = 2016;  // staged texels: 7 workgroups per CU beside the sums
+// Tiles of a step from which its views of several lights go this way: those
+// that fill the GPU once.  Below, a view's lights one after the other leave it
+// idle, and all of them at once, then the composite, are faster.  Latency in us,
+// lights in turn / at once: 8 requests of 300 fragments (16 tiles in all), 8
+// lights 260 / 146; one of 960 x 540 (510), 8 lights 138 / 112; of 1280 x 720
+// (920), 4 lights 107 / 102, 8 155 / 133; of 1920 x 1080 (2040), 4 lights 125 /
+// 142, 8 190 / 206.  One light is its own composite: in turn always.
+constexpr int64_t kViewTiles = 7 * 256;
 constexpr int kArgViews = 20;
 constexpr int kArgViewLights = 40;
 
@@ -291,7 +299,8 @@ int64_t request_work(const EngineReq &R) {
     return b;
 }
 
-// Can the request's lights and composite run as one job of the view kernel?
+// Can the request's lights and composite run as one job of the view kernel
+// (the step's size decides whether they do)?
 // A composite is wanted, every light's pass is the tile pass (no RPCF), and
 // the view fits the 32-bit index form.
 bool is_view_job(const EngineReq &R) {
@@ -395,6 +404,7 @@ bool rbsm_engine::step_launch() {
     std::vector<std::pair<EngineReq *, int>> rpcf_jobs, tile_jobs;  // (request, light)
     std::vector<rbsm::CompJob> comps;
     std::vector<EngineReq *> views;  // requests whose lights and composite are one job of the view kernel
+    int64_t view_tiles = 0;          // of the requests that can be
     int n_jobs = 0;
     size_t taken = 0;
     for (; taken < admitted.size(); ++taken) {
@@ -403,7 +413,11 @@ bool rbsm_engine::step_launch() {
         if (n_jobs + q.n_lights > rbsm::kServeMaxJobs || (int)batch.size() >= rbsm::kServeMaxReqs) break;
         n_jobs += q.n_lights;
         batch.push_back(R);
-        if (is_view_job(*R)) {
+        if (is_view_job(*R)) view_tiles += job_layout(q.n, q.view_width, rbsm::kServeTileW).tiles;
+    }
+    for (EngineReq *R : batch) {
+        const rbsm_request &q = R->req;
+        if (is_view_job(*R) && (q.n_lights == 1 || view_tiles >= rbsm::kViewTiles)) {
             views.push_back(R);
             continue;
         }
