@@ -143,11 +143,15 @@ __device__ __forceinline__ float win_axis(WalkEnd n, WalkEnd p, float f, const l
 // -> 0.88 / 0.88, 640x360 r = 32 (one lane per fragment before) 26.5 -> 1.4.
 // Keeping both kinds of words at 16 bits up to NR = 16 gives 28 waves per CU.
 // Waves per SIMD: what LDS leaves room for.  MULTI at NR = 24 fits 6 workgroups
-// (3 waves per SIMD, 163 VGPRs): held to 4 waves it spilled 24 registers, and
-// 762 MB of a 4K r = 15 frame's writes were scratch (720p r = 21 1174 us, now
-// 1109; r = 32 2084, now 1965).
+// (3 waves per SIMD, 164 VGPRs): held to 4 waves it spilled 24 registers, and
+// 762 MB of a 4K r = 15 frame's writes were scratch (720p r = 21 1174 us against
+// 1109, r = 32 2084 against 1965).  MULTI at NR = 20 spills 5 registers at 4
+// waves, NR = 16 3 at 7; a wave fewer is slower (r = 5 522 -> 534 us at 6).
 template <int NR, bool MULTI>
-__global__ __launch_bounds__(kRpcfT) __attribute__((amdgpu_waves_per_eu(NR <= 16 ? 7 : MULTI && NR == 24 ? 3 : 4))) void
+constexpr int kWinWaves = NR <= 16 ? 7 : MULTI && NR == 24 ? 3 : 4;  // per SIMD; a CU: 4 SIMDs, 2 waves a workgroup
+
+template <int NR, bool MULTI>
+__global__ __launch_bounds__(kRpcfT) __attribute__((amdgpu_waves_per_eu(kWinWaves<NR, MULTI>))) void
 rpcf_window_kernel(
     MapView m, const float *__restrict__ frags, int64_t n, int64_t vw, int64_t tiles_x, int tw_log2, float bias,
     int maxd, int r, int parts, int part_side, int cap, int list_cap, int chunk_log2, float *__restrict__ out) {
@@ -529,9 +533,12 @@ rpcf_window_kernel(
 // Launch of the window kernel: a band for a tile whose texel footprint spans up
 // to 17 x 17 texels (the column words' room where that is more), tiles dealt
 // to the XCDs in chunks of 32 (their cost varies with the edges; contiguous
-// ranges left XCDs idle: 4K r = 5 5-7% slower).  The list is as long as LDS
-// allows without losing a workgroup per CU: r = 13 fits five with 128 terms,
-// r = 14 never more than four.
+// ranges left XCDs idle: 4K r = 5 5-7% slower).  The list of terms is the
+// longest of 128, 192, .. 512 with which a CU still holds as many workgroups as
+// with the shortest (longer lists are evaluated in fewer, fuller batches).  It
+// follows the radius' words and, by the reciprocals, MAXDIST.  Against 192 for
+// most radii, where r = 21 and 32 lost a workgroup: 720p r = 21 1136 -> 1063 us,
+// r = 32 2018 -> 1903, r = 5, 9, 12 and 18 1 to 2% less.
 template <int NR, bool MULTI>
 void launch_window(const MapView &mv, const float *frags, int64_t n, int64_t view_width, float bias, int maxd, int r,
                    int parts, float *out, hipStream_t stream) {
@@ -540,8 +547,17 @@ void launch_window(const MapView &mv, const float *frags, int64_t n, int64_t vie
     const int N = NR <= 16 ? NR : side + 2;
     const int words = 2 * N * 64 * (int)sizeof(Word), extra = (NR - N) * 64 * (int)sizeof(Word);  // bytes
     const int band = std::max(words - 2 * extra, (NR + 16) * (NR + 16) * 4);
-    const int list = r == 13 ? 128 : (r == 14 ? 512 : 192);
-    const size_t lds = (size_t)(words + 2 * extra + band + 4 * (2 * maxd + 2) + 2 * 2 * list);
+    const int fixed = words + 2 * extra + band + 4 * (2 * maxd + 2);  // bytes beside the lists
+    constexpr int kCuLds = 160 * 1024, kLdsUnit = 1280;               // of a CU; what it is given out in
+    constexpr int kStatic = 2 * 6 * 4 + kRpcfT * 8 + 2 * kWinLate * 2;
+    constexpr int kMost = 2 * kWinWaves<NR, MULTI>;                   // workgroups the registers leave room for
+    auto groups = [&](int list) {
+        const int units = (fixed + 2 * 2 * list + kStatic + kLdsUnit - 1) / kLdsUnit;
+        return std::min(kMost, kCuLds / (units * kLdsUnit));
+    };
+    int list = 128;
+    while (list < 512 && groups(list + 64) == groups(128)) list += 64;
+    const size_t lds = (size_t)(fixed + 2 * 2 * list);
     const int64_t vw = view_width > 0 ? view_width : n;
     const int tw_log2 = view_width > 0 ? 4 : 7;  // 16 x 8 pixels, or 128 consecutive fragments
     const int th = kRpcfT >> tw_log2;
@@ -557,7 +573,7 @@ void launch_window(const MapView &mv, const float *frags, int64_t n, int64_t vie
 // goes in parts of at most 22 x 22 terms, whose 24 x 24 windows leave LDS for
 // 6 workgroups per CU; parts of 30 terms (32 x 32 windows) leave it for 4.
 // Parts of at most 18 terms a side (r = 15..17 in two, 22..26 in three) take 20
-// x 20 windows, which test 30% fewer texels and leave LDS for 8 workgroups: 720p r =
+// x 20 windows, which test 30% fewer texels and leave LDS for 7 or 8: 720p r =
 // 15 787 -> 709 us, r = 22 1421 -> 1178 (24 x 24 at 4 waves per SIMD before).
 inline void launch_rpcf(const MapView &mv, const float *frags, int64_t n, int64_t view_width, float bias, int maxd,
                         int r, float *out, hipStream_t stream) {
