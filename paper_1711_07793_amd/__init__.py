@@ -202,7 +202,10 @@ def _stream(stream) -> int:
         # the current stream's handle without a Stream object around it (0.2 us a
         # call instead of 2.9, a third of a small call's time on the host)
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:  # private names of torch: without them, the Stream object
+                pass
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
