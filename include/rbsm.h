@@ -131,8 +131,7 @@ int rbsm_footprint(const float *shadow_map, const float *frags, int64_t n, const
  * project's autotuner searches.
  */
 typedef struct {
-    int32_t tile_w;     /* screen-tile width in pixels: 16, 32 or 64 (height 1024 / tile_w);
-                           ignored by the single-pass entry points when view_width is 0 */
+    int32_t tile_w;     /* screen-tile width in pixels: 16, 32 or 64 (height 1024 / tile_w) */
     int32_t apron;      /* texels staged around the tile's texel box, 1..8 */
     int32_t lds_cap;    /* LDS texel capacity per workgroup, 256..12288, or 0:
                            nothing staged, every texel read from global memory */
@@ -159,9 +158,11 @@ rbsm_tuning rbsm_default_tuning(void);
  * rbsm_visibility (mode 0, out = uint8_t[n]) or rsmss_visibility with
  * kernel_radius 0 (mode 1, out = float[n]) under an explicit tuning.
  * Arguments as those entry points; tune must be valid (RBSM_ERR_INVALID_ARG
- * otherwise).  This entry point honours tile_w, apron, lds_cap and
- * persistent; walk_first and walk_block must be 0 or their defaults (the
- * walk blocking is searched in plans, whose kernels are built for each).
+ * otherwise).  For views this entry point honours tile_w, apron, lds_cap,
+ * persistent and xcd_chunk; lists (view_width 0) run a lane per fragment,
+ * without tiles, whatever these say.  walk_first and walk_block must be 0 or
+ * their defaults (the walk blocking is searched in plans, whose kernels are
+ * built for each).
  */
 int rbsm_pass_tuned(int32_t mode, const float *shadow_map, const float *frags, int64_t n,
                     const rbsm_params *p, const rbsm_tuning *tune, void *out, hipStream_t stream);
