@@ -27,7 +27,7 @@
 // index, among equal depths.
 //
 // Bound by the write of the map on large maps (8192^2: 41-56 us by run, median
-// 47, 71 on some machines for reasons not known; the plane alone 39), by the
+// 47, 71 in some processes for reasons not known; the plane alone 39), by the
 // latency of load, bounds and classification on small ones (1024^2: 8 us, the
 // plane alone 4).  A workgroup per 64 x 64, 32 x 32 or 16 x
 // 16 tile with the primitives' indices listed in LDS and every coordinate
